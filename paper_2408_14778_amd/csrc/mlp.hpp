@@ -48,6 +48,28 @@ void launch_colsum(int rows, int cols, const void* G, float* out, hipStream_t st
 bool launch_mlp_forward(int M, int F, int H, int A, const void* X, const void* W1P, const float* b1,
                         const void* W2P, const float* b2, const void* W3T, const float* b3,
                         float* Z, hipStream_t st);
+// Whether the fused forward pass takes a shape: F a multiple of 16 up to 128, H 64, 128 or 256, A
+// at most 8, X 16-byte aligned.
+bool mlp_fused_shape(int F, int H, int A, const void* X);
+// A training step in three launches for those shapes and at least 64 rows: the rows' forward and
+// backward pass, the gradients' partials, and the update of the weights and all their copies. The
+// weights, moments and gradients equal those of the per-layer launches bit for bit. False:
+// nothing launched.
+constexpr int kMaxLossParts = 4096;  // workgroups of the first launch
+struct TrainArgs {
+    const void* x;
+    const float *target, *mask;
+    const __bf16 *W1P, *W2P, *W2B, *W3T;
+    const float *b1, *b2, *b3;
+    __bf16 *A1, *A2, *dZ3, *dZ2, *dZ1;
+    float* part;  // mlp_train_part_floats
+    float* loss;
+    float *w, *g, *m, *v;
+    __bf16 *wb, *wbT, *wbP;
+    float lr, beta1, beta2, eps, c1, c2;
+};
+int64_t mlp_train_part_floats(int F, int H, int A);
+bool launch_mlp_train(int B, int F, int H, int A, const TrainArgs& t, hipStream_t st);
 // The K x H weights W, given transposed (WT, H x K), packed in MFMA B-fragment order for
 // launch_mlp_forward (K a multiple of 16, H of 32; otherwise nothing is written).
 void launch_pack_fragments(int K, int H, const void* WT, void* dst, hipStream_t st);

@@ -36,7 +36,7 @@ size_t layout(cfr_mlp& n, void* base, int32_t F, int32_t H, int32_t A, int32_t m
     n.v = static_cast<float*>(take(P * 4));
     n.wb = static_cast<__bf16*>(take(P * 2));
     n.wbT = static_cast<__bf16*>(take(P * 2));
-    n.wbP = static_cast<__bf16*>(take(P * 2));
+    n.wbP = static_cast<__bf16*>(take((int64_t{F} + 2 * int64_t{H}) * H * 2));
     n.A1 = static_cast<__bf16*>(take(int64_t{maxB} * H * 2));
     n.A2 = static_cast<__bf16*>(take(int64_t{maxB} * H * 2));
     n.dZ2 = static_cast<__bf16*>(take(int64_t{maxB} * H * 2));
@@ -44,10 +44,12 @@ size_t layout(cfr_mlp& n, void* base, int32_t F, int32_t H, int32_t A, int32_t m
     n.dZ3 = static_cast<__bf16*>(take(int64_t{maxB} * A * 2));
     n.Z3 = static_cast<float*>(take(int64_t{maxB} * A * 4));
     n.loss = static_cast<float*>(take(4));
-    // split-K partials of the weight gradients, or the column-sum partials of the bias gradients
+    // partials of the gradients: all of a fused step's at once, or one layer's split-K or
+    // column-sum partials at a time
     n.part = static_cast<float*>(
-        take(std::max(int64_t{cfr::kMaxSplits} * std::max(F, H) * std::max(H, A),
-                      int64_t{cfr::kColsumMaxSplits} * std::max(H, A)) * 4));
+        take(std::max({int64_t{cfr::kMaxSplits} * std::max(F, H) * std::max(H, A),
+                       int64_t{cfr::kColsumMaxSplits} * std::max(H, A),
+                       cfr::mlp_train_part_floats(F, H, A)}) * 4));
     return (off + 255) & ~size_t{255};
 }
 
@@ -84,7 +86,9 @@ void transpose_weights(cfr_mlp* n) {
     cfr::launch_transpose_bf16(n->H, n->H, n->wb + o[2], n->wbT + t[1], n->st);
     cfr::launch_transpose_bf16(n->H, n->A, n->wb + o[4], n->wbT + t[2], n->st);
     cfr::launch_pack_fragments(n->F, n->H, n->wbT + t[0], n->wbP, n->st);
-    cfr::launch_pack_fragments(n->H, n->H, n->wbT + t[1], n->wbP + int64_t{n->F} * n->H, n->st);
+    const int64_t p2 = int64_t{n->F} * n->H, p3 = p2 + int64_t{n->H} * n->H;
+    cfr::launch_pack_fragments(n->H, n->H, n->wbT + t[1], n->wbP + p2, n->st);
+    cfr::launch_pack_fragments(n->H, n->H, n->wb + o[2], n->wbP + p3, n->st);
 }
 
 }  // namespace
@@ -179,32 +183,45 @@ int cfr_mlp_train_step(cfr_mlp* n, const void* x, const float* target, const flo
     int64_t o[7];
     offsets(n->F, n->H, n->A, o);
     const int F = n->F, H = n->H, A = n->A;
-    forward(n, x, B);
-    MLP_TRY(hipMemsetAsync(n->loss, 0, 4, n->st), "loss reset");
-    cfr::launch_softmax_xent(B, A, n->Z3, target, mask, n->dZ3, n->loss, n->st);
-    // layer 3
-    cfr::launch_gemm(H, A, B, n->A2, 1, H, n->dZ3, A, 1, nullptr, 0, nullptr, n->g + o[4], nullptr,
-                     A, n->st, n->part);
-    cfr::launch_colsum(B, A, n->dZ3, n->g + o[5], n->st, n->part);
-    cfr::launch_gemm(B, H, A, n->dZ3, A, 1, n->wb + o[4], 1, A, nullptr, 2, n->A2, nullptr, n->dZ2,
-                     H, n->st);
-    // layer 2
-    cfr::launch_gemm(H, H, B, n->A1, 1, H, n->dZ2, H, 1, nullptr, 0, nullptr, n->g + o[2], nullptr,
-                     H, n->st, n->part);
-    cfr::launch_colsum(B, H, n->dZ2, n->g + o[3], n->st, n->part);
-    cfr::launch_gemm(B, H, H, n->dZ2, H, 1, n->wb + o[2], 1, H, nullptr, 2, n->A1, nullptr, n->dZ1,
-                     H, n->st);
-    // layer 1
-    cfr::launch_gemm(F, H, B, x, 1, F, n->dZ1, H, 1, nullptr, 0, nullptr, n->g + o[0], nullptr, H,
-                     n->st, n->part);
-    cfr::launch_colsum(B, H, n->dZ1, n->g + o[1], n->st, n->part);
-    // Adam
     n->step += 1;
-    const float b1 = 0.9f, b2 = 0.999f;
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
     const float c1 = 1.0f - std::pow(b1, static_cast<float>(n->step));
     const float c2 = 1.0f - std::pow(b2, static_cast<float>(n->step));
-    cfr::launch_adam(n->n_params, n->w, n->g, n->m, n->v, n->wb, lr, b1, b2, 1e-8f, c1, c2, n->st);
-    transpose_weights(n);
+    int64_t tr[3];
+    cfr::transposed_offsets(F, H, A, tr);
+    cfr::TrainArgs ta{};
+    ta.x = x; ta.target = target; ta.mask = mask;
+    ta.W1P = n->wbP; ta.W2P = n->wbP + int64_t{F} * H; ta.W2B = ta.W2P + int64_t{H} * H;
+    ta.W3T = n->wbT + tr[2];
+    ta.b1 = n->w + o[1]; ta.b2 = n->w + o[3]; ta.b3 = n->w + o[5];
+    ta.A1 = n->A1; ta.A2 = n->A2; ta.dZ3 = n->dZ3; ta.dZ2 = n->dZ2; ta.dZ1 = n->dZ1;
+    ta.part = n->part; ta.loss = n->loss;
+    ta.w = n->w; ta.g = n->g; ta.m = n->m; ta.v = n->v;
+    ta.wb = n->wb; ta.wbT = n->wbT; ta.wbP = n->wbP;
+    ta.lr = lr; ta.beta1 = b1; ta.beta2 = b2; ta.eps = eps; ta.c1 = c1; ta.c2 = c2;
+    if (!cfr::launch_mlp_train(B, F, H, A, ta, n->st)) {
+        forward(n, x, B);
+        MLP_TRY(hipMemsetAsync(n->loss, 0, 4, n->st), "loss reset");
+        cfr::launch_softmax_xent(B, A, n->Z3, target, mask, n->dZ3, n->loss, n->st);
+        // layer 3
+        cfr::launch_gemm(H, A, B, n->A2, 1, H, n->dZ3, A, 1, nullptr, 0, nullptr, n->g + o[4],
+                         nullptr, A, n->st, n->part);
+        cfr::launch_colsum(B, A, n->dZ3, n->g + o[5], n->st, n->part);
+        cfr::launch_gemm(B, H, A, n->dZ3, A, 1, n->wb + o[4], 1, A, nullptr, 2, n->A2, nullptr,
+                         n->dZ2, H, n->st);
+        // layer 2
+        cfr::launch_gemm(H, H, B, n->A1, 1, H, n->dZ2, H, 1, nullptr, 0, nullptr, n->g + o[2],
+                         nullptr, H, n->st, n->part);
+        cfr::launch_colsum(B, H, n->dZ2, n->g + o[3], n->st, n->part);
+        cfr::launch_gemm(B, H, H, n->dZ2, H, 1, n->wb + o[2], 1, H, nullptr, 2, n->A1, nullptr,
+                         n->dZ1, H, n->st);
+        // layer 1
+        cfr::launch_gemm(F, H, B, x, 1, F, n->dZ1, H, 1, nullptr, 0, nullptr, n->g + o[0], nullptr,
+                         H, n->st, n->part);
+        cfr::launch_colsum(B, H, n->dZ1, n->g + o[1], n->st, n->part);
+        cfr::launch_adam(n->n_params, n->w, n->g, n->m, n->v, n->wb, lr, b1, b2, eps, c1, c2, n->st);
+        transpose_weights(n);
+    }
     MLP_TRY(hipGetLastError(), "train launch");
     if (loss != nullptr) {
         MLP_TRY(hipMemcpyAsync(loss, n->loss, 4, hipMemcpyDeviceToHost, n->st), "loss copy");

@@ -17,12 +17,12 @@ struct cfr_mlp {
     // the weight matrices transposed, [W1^T (H x F) | W2^T (H x H) | W3^T (A x H)], refreshed
     // with wb: the forward pass reads both GEMM operands along k
     __bf16* wbT;
-    // W1 and W2 packed in MFMA fragment order for the fused forward pass, [W1 | W2]
+    // W1, W2 and W2^T packed in MFMA fragment order for the fused passes, [W1 | W2 | W2^T]
     __bf16* wbP;
     // activations
     __bf16 *A1, *A2, *dZ3, *dZ2, *dZ1;
     float *Z3, *loss;
-    float* part;  // split-K partials: kMaxSplits * max(F, H) * max(H, A) floats
+    float* part;  // partials of the weight and bias gradients
     int64_t step;
 };
 
