@@ -1,0 +1,359 @@
+// Host plan of the resident iteration: see resident_plan.hpp.
+#include "resident_plan.hpp"
+
+#include <algorithm>
+#include <atomic>
+#include <thread>
+
+namespace cfr {
+
+namespace {
+
+// Nodes that a bin should hold at least, when there are CUs to spare: below this its levels are
+// all latency, and more workgroups only make the barrier dearer.
+constexpr int64_t kBinNodes = 3000;
+
+int64_t columns(const ResSizes& z) { return z.players > 0 ? z.players : 1; }
+int64_t planes(const ResSizes& z) { return z.players > 0 ? z.players : 2; }
+
+}  // namespace
+
+int32_t resident_max_bins(const ResSizes& z) {
+    const bool block = z.players == 0 && z.real_bytes == 4 && z.level_pure;
+    return 1 + (block ? kResRoundsBlock : kResRounds) * (kResTeam - 1);
+}
+
+bool resident_fits(const ResSizes& z) {
+    return z.decision > 0 && z.depth >= 1 && z.depth <= kResMaxDepth &&
+           z.max_actions <= kResMaxActions && z.pairs + z.chance_pairs < (int64_t{1} << 28) &&
+           z.players < 15 &&
+           z.real_bytes * (columns(z) * z.nodes + planes(z) * z.decision) <=
+               kResLds * resident_max_bins(z);
+}
+
+int64_t resident_max_table(const ResSizes& z) { return int64_t{resident_max_bins(z)} * (z.depth + 3); }
+int64_t resident_max_roots(const ResSizes& z) { return std::min<int64_t>(kResTrunk, z.decision); }
+int64_t resident_max_path(const ResSizes& z) { return kResPath * resident_max_roots(z); }
+
+bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResSizes& z,
+                    ResPlan& P) {
+    const int64_t N = L.N;
+    const int32_t D = L.D;
+    const int64_t cols = columns(z), pl = planes(z), real = z.real_bytes;
+    P = ResPlan{};
+    if (!resident_fits(z)) return false;
+    for (int64_t v = 0; v < N; ++v)
+        if (L.node_player[v] == 0 && L.child_begin[v + 1] - L.child_begin[v] > kResMaxFan) return false;
+    int64_t con = 0;
+    for (int64_t h = 0; h < L.Hp; ++h)
+        con += static_cast<int64_t>(L.member_offset[h + 1] - L.member_offset[h]) *
+               res_stride(L.q_offset[h + 1] - L.q_offset[h], z.real_bytes);
+    if (con >= (int64_t{1} << 31)) return false;
+    P.contributions = con;
+    const int64_t nd = z.decision;
+    // a bin's LDS: values and edge probabilities, reach and short records
+    auto bin_bytes = [&](int64_t n, int64_t d) { return real * ((cols + 1) * n + pl * d) + 8 * d; };
+    auto edge_of = [&](int64_t v) {
+        const int32_t p = L.parent[v];
+        if (L.node_player[p] == 0) return L.node_edge[v];
+        const int32_t h = L.node_infoset[p];
+        return q_of[h] + (L.node_edge[v] - L.q_offset[h]);
+    };
+    std::vector<int8_t> level(N, 0);
+    for (int32_t l = 0; l <= D; ++l)
+        for (int32_t v = L.level_offset[l]; v < L.level_offset[l + 1]; ++v)
+            level[v] = static_cast<int8_t>(l);
+    // owner of every node: its bin (0: the trunk); bins' roots in order
+    std::vector<int32_t> roots, bin_root{0, 0}, in_trunk, sn, sd;
+    std::vector<int8_t> trunk(N, 0);
+    const int64_t solo = real * (cols * N + pl * nd + 3 * z.pairs + z.chance_pairs + con) + 16 * nd;
+    if (N <= 65535 && solo <= kResLds) {
+        P.mode = RES_SOLO;
+        P.bins = 1;
+        roots.push_back(0);
+        bin_root = {0, 1};
+    } else {
+        // nodes and decision nodes of every subtree
+        sn.assign(N, 1);
+        sd.assign(N, 0);
+        for (int64_t v = N - 1; v >= 0; --v) {
+            sd[v] += L.node_player[v] >= 0 ? 1 : 0;
+            if (v > 0) {
+                sn[L.parent[v]] += sn[v];
+                sd[L.parent[v]] += sd[v];
+            }
+        }
+        int64_t first_want = std::min<int64_t>(kResTeam - 1, std::max<int64_t>(1, N / kBinNodes));
+        // one XCD with the trunk
+        if (first_want >= kResXcd && first_want < 2 * kResXcd) first_want = kResXcd - 1;
+        bool found = false;
+        // more bins until they fit: up to one per workgroup, then whole rounds of them
+        for (int64_t want = first_want; want < resident_max_bins(z) && !found;
+             want = want < kResTeam - 1 ? std::min<int64_t>(kResTeam - 1, want + want / 8 + 1)
+                                        : want + kResTeam - 1) {
+            // subtrees of at most a fraction of a bin: small ones balance, large ones leave a
+            // small trunk
+            const int64_t even = (N + want - 1) / want;
+            for (int64_t t = std::max<int64_t>(even / 16, 16); t <= even && !found; t *= 2) {
+                // the trunk, level by level from the root
+                roots.clear();
+                for (int32_t v : in_trunk) trunk[v] = 0;
+                in_trunk.assign(1, 0);
+                trunk[0] = 1;
+                int64_t tn = 1;
+                int32_t deepest = 0;
+                for (size_t i = 0; i < in_trunk.size() && tn <= 65535; ++i) {
+                    const int32_t p = in_trunk[i];
+                    for (int32_t v = L.child_begin[p]; v < L.child_begin[p + 1]; ++v) {
+                        ++tn;
+                        if (L.node_player[v] < 0) continue;
+                        if (sn[v] > t) {
+                            trunk[v] = 1;
+                            in_trunk.push_back(v);
+                        } else {
+                            roots.push_back(v);
+                            deepest = std::max<int32_t>(deepest, level[v]);
+                        }
+                    }
+                }
+                const int64_t td = static_cast<int64_t>(in_trunk.size());
+                if (roots.size() < 2 || static_cast<int64_t>(roots.size()) > kResTrunk ||
+                    deepest > kResPath || tn > 65535 || bin_bytes(tn, td) > kResLds)
+                    continue;
+                // by level and first edge: in the public-block order the members of an infoset
+                // then lie in few bins
+                std::sort(roots.begin(), roots.end(), [&](int32_t a, int32_t b) {
+                    if (level[a] != level[b]) return level[a] < level[b];
+                    const int32_t ea = edge_of(L.child_begin[a]), eb = edge_of(L.child_begin[b]);
+                    return ea != eb ? ea < eb : a < b;
+                });
+                int64_t total = 0, most = 0;
+                for (int32_t v : roots) {
+                    total += sn[v];
+                    most = std::max<int64_t>(most, sn[v]);
+                }
+                for (int64_t cap = std::max((total + want - 1) / want, most); cap < 2 * total + 2;
+                     cap += cap / 32 + 1) {
+                    bin_root.assign(1, 0);
+                    // (every workgroup's arrays have room for the largest bin's nodes and ranks)
+                    int64_t n = 0, d = 0, most_n = tn, most_d = td;
+                    bool fits = true;
+                    for (size_t i = 0; i < roots.size(); ++i) {
+                        const int32_t v = roots[i];
+                        if (i == 0 || n + sn[v] > cap) {
+                            bin_root.push_back(static_cast<int32_t>(i));
+                            n = d = 0;
+                        }
+                        n += sn[v];
+                        d += sd[v];
+                        most_n = std::max(most_n, n);
+                        most_d = std::max(most_d, d);
+                        fits = most_n <= 65535 && most_d <= 65535 && bin_bytes(most_n, most_d) <= kResLds;
+                        if (!fits) break;
+                    }
+                    if (!fits) break;  // larger bins fit less
+                    if (static_cast<int64_t>(bin_root.size()) - 1 <= want) {
+                        found = true;
+                        P.mode = RES_TEAM;
+                        break;
+                    }
+                }
+            }
+        }
+        if (!found) return false;
+        P.bins = static_cast<int32_t>(bin_root.size());
+        bin_root.push_back(static_cast<int32_t>(roots.size()));
+        P.roots = static_cast<int32_t>(roots.size());
+        for (int32_t v : roots) P.path_len = std::max<int32_t>(P.path_len, level[v]);
+    }
+    const bool team = P.mode == RES_TEAM;
+    const int32_t W = D + 3;
+    P.table.assign(static_cast<size_t>(P.bins) * W, Rec4{0, 0, 0, 0});
+    P.rec.resize(nd);
+    P.slot.assign(nd, 0);
+    P.reach_c.resize(nd);
+    P.rank_node.resize(nd);
+    P.node.resize(N + P.roots);
+    P.root_rank.resize(P.roots);
+    P.ext.resize(P.roots);
+    P.path.assign(static_cast<size_t>(P.roots) * P.path_len, 0);
+    std::vector<int32_t> glog(D + 1, 0);
+    for (int32_t l = 0; l < D; ++l) {
+        // lanes per node: the level's largest chance fan-out rounded up to a power of two, at
+        // most a wavefront; a workgroup per node past 256
+        int32_t kmax = 1;
+        for (int32_t v = L.level_offset[l]; v < L.level_offset[l + 1]; ++v)
+            if (L.node_player[v] == 0)
+                kmax = std::max(kmax, L.child_begin[v + 1] - L.child_begin[v]);
+        int32_t g = 0;
+        while (g < 6 && (1 << g) < kmax) ++g;
+        glog[l] = kmax > 256 ? kResWide : g;
+    }
+    // chance products (rounded to float after every factor in single precision, as the level by
+    // level launches form them)
+    const bool f64 = real == 8;
+    std::vector<double> rc(N, 1.0);
+    for (int64_t v = 1; v < N; ++v) {
+        if (L.node_player[v] < 0) continue;  // (terminal nodes need none)
+        const int32_t p = L.parent[v];
+        double x = rc[p];
+        if (L.node_player[p] == 0) {
+            const int64_t i = L.node_edge[v] - L.Qp;
+            x = f64 ? x * L.chance_prob64[i]
+                    : static_cast<double>(static_cast<float>(x) * L.chance_prob[i]);
+        }
+        rc[v] = x;
+    }
+    // infosets: the trunk's first, then by pair (through the pairs: no sort); their contribution
+    // slots in that order
+    std::vector<int8_t> of_trunk(L.Hp, 0);
+    if (team)
+        for (int32_t v : in_trunk)
+            if (L.node_player[v] > 0) of_trunk[L.node_infoset[v]] = 1;
+    std::vector<int32_t> order, at_pair(L.Qp, -1);
+    order.reserve(L.Hp);
+    for (int64_t h = 0; h < L.Hp; ++h) at_pair[q_of[h]] = static_cast<int32_t>(h);
+    for (int pass = 1; pass >= 0; --pass)
+        for (int64_t q = 0; q < L.Qp; ++q)
+            if (at_pair[q] >= 0 && of_trunk[at_pair[q]] == pass) order.push_back(at_pair[q]);
+    P.sets.resize(L.Hp);
+    std::vector<int32_t> slot(N, 0);
+    int64_t at = 0;
+    for (int64_t i = 0; i < L.Hp; ++i) {
+        const int32_t h = order[i];
+        const int32_t m0 = L.member_offset[h], n = L.member_offset[h + 1] - m0;
+        const int32_t k = L.q_offset[h + 1] - L.q_offset[h];
+        P.trunk_sets += of_trunk[h];
+        P.max_actions = std::max(P.max_actions, k);
+        P.sets[i] = Rec4{q_of[h], static_cast<int32_t>(at), n, k | (L.infoset_player[h] << 24)};
+        for (int32_t j = 0; j < n; ++j)
+            slot[L.members[m0 + j]] =
+                static_cast<int32_t>(at + static_cast<int64_t>(j) * res_stride(k, z.real_bytes));
+        at += static_cast<int64_t>(n) * res_stride(k, z.real_bytes);
+    }
+    P.mean_members = L.Hp > 0 ? static_cast<int32_t>(L.n_members / L.Hp) : 0;
+    // where each bin's ranks and nodes begin
+    std::vector<int64_t> rbase_of(P.bins, 0), nbase_of(P.bins, 0);
+    if (team) {
+        int64_t rb = static_cast<int64_t>(in_trunk.size()), nb = 1;
+        for (int32_t v : in_trunk) nb += L.child_begin[v + 1] - L.child_begin[v];
+        for (int32_t b = 1; b < P.bins; ++b) {
+            rbase_of[b] = rb;
+            nbase_of[b] = nb;
+            for (int32_t x = bin_root[b]; x < bin_root[b + 1]; ++x) {
+                rb += sd[roots[x]];
+                nb += sn[roots[x]];
+            }
+        }
+    }
+    // the bins: local numbers level by level, records (the trunk first: its leaves are numbered
+    // again in their own bins; the others on several threads)
+    std::vector<int32_t> lnode(N, -1), lrank(N, -1);
+    std::vector<int32_t> bin_nodes(P.bins, 0), bin_ranks(P.bins, 0);
+    auto fill_bin = [&](int32_t b) {
+        std::vector<int32_t> now, next;
+        const int64_t rbase = rbase_of[b], nbase = nbase_of[b];
+        Rec4* t = P.table.data() + static_cast<size_t>(b) * W;
+        const bool is_trunk = team && b == 0;
+        int32_t r0 = is_trunk ? 0 : team ? bin_root[b] : 0, r1 = is_trunk ? 0 : team ? bin_root[b + 1] : 1;
+        const int32_t first_root = r0, end_root = r1;
+        int32_t n = 0, r = 0, l0 = -1, l1 = -1;
+        now.clear();
+        for (int32_t l = 0; l <= D; ++l) {
+            // the children of the bin's nodes of the level above, then the roots of this one
+            next.clear();
+            for (int32_t p : now)
+                for (int32_t c = L.child_begin[p]; c < L.child_begin[p + 1]; ++c) next.push_back(c);
+            if (is_trunk && l == 0) next.push_back(0);
+            while (r0 < r1 && level[roots[r0]] == l) next.push_back(roots[r0++]);
+            t[l] = Rec4{n, r, l < D ? glog[l] : 0, 0};
+            for (int32_t v : next) {
+                lnode[v] = n;
+                P.node[nbase + n++] = v;
+            }
+            // (the roots of other bins are leaves of the trunk)
+            now.clear();
+            for (int32_t v : next)
+                if (L.node_player[v] >= 0 && (!is_trunk || trunk[v])) now.push_back(v);
+            for (int32_t v : now)
+                if (L.node_player[v] > 0) lrank[v] = r++;
+            for (int32_t v : now)
+                if (L.node_player[v] == 0) {
+                    lrank[v] = r++;
+                    ++t[l].w;
+                }
+            if (!now.empty()) {
+                l0 = l0 < 0 ? l : l0;
+                l1 = l;
+            }
+        }
+        if (is_trunk)
+            for (int32_t x = 0; x < P.roots; ++x) P.ext[x] = lnode[roots[x]];
+        t[D + 1] = Rec4{static_cast<int32_t>(rbase), n, r, static_cast<int32_t>(nbase)};
+        t[D + 2] = Rec4{l0, l1 - l0 + 1, team ? first_root : 0, team ? end_root : 0};
+        bin_nodes[b] = n;
+        bin_ranks[b] = r;
+        for (int32_t i = 0; i < n; ++i) {
+            const int64_t v = P.node[nbase + i];
+            if (L.node_player[v] < 0 || (is_trunk && !trunk[v])) continue;
+            const int32_t d = lrank[v];
+            const int32_t c0 = L.child_begin[v], k = L.child_begin[v + 1] - c0;
+            const int32_t who = L.node_player[v];
+            const int32_t p = L.parent[v];
+            // a subtree's root has no parent in its bin
+            const bool root = v > 0 && team && !is_trunk && trunk[p];
+            const uint32_t actor = root ? 15u : v == 0 ? 15u : static_cast<uint32_t>(L.node_player[p]);
+            Rec4& q = P.rec[rbase + d];
+            q.x = static_cast<int32_t>(static_cast<uint32_t>(lnode[c0]) |
+                                       (static_cast<uint32_t>(lnode[v]) << 16));
+            q.y = static_cast<int32_t>(static_cast<uint32_t>(edge_of(c0)) |
+                                       (static_cast<uint32_t>(who) << 28));
+            q.z = static_cast<int32_t>((root || v == 0 ? 0u : static_cast<uint32_t>(lrank[p])) |
+                                       (actor << 16) | (static_cast<uint32_t>(k) << 20));
+            q.w = v == 0 ? 0 : edge_of(v);
+            P.slot[rbase + d] = slot[v];
+            P.reach_c[rbase + d] = rc[v];
+            P.rank_node[rbase + d] = static_cast<int32_t>(v);
+        }
+        if (team && !is_trunk)
+            for (int32_t x = first_root; x < end_root; ++x) {
+                int64_t u = roots[x];
+                P.root_rank[x] = lrank[u];
+                for (int32_t q = level[u] - 1; q >= 0; --q) {
+                    const int32_t p = L.parent[u];
+                    P.path[static_cast<size_t>(q) * P.roots + x] =
+                        static_cast<int32_t>(static_cast<uint32_t>(edge_of(u)) |
+                                             (static_cast<uint32_t>(L.node_player[p]) << 28));
+                    u = p;
+                }
+            }
+    };
+    fill_bin(0);
+    std::atomic<int32_t> at_bin{1};
+    std::atomic<bool> failed{false};
+    auto work = [&] {
+        try {
+            for (int32_t b; (b = at_bin.fetch_add(8)) < P.bins;)
+                for (int32_t i = b; i < std::min(P.bins, b + 8); ++i) fill_bin(i);
+        } catch (...) {  // out of memory: the game is not resident
+            failed = true;
+        }
+    };
+    std::vector<std::thread> pool;
+    if (N > 100000)
+        try {
+            for (unsigned i = 1; i < std::min(8u, std::thread::hardware_concurrency()); ++i)
+                pool.emplace_back(work);
+        } catch (...) {  // fewer threads
+        }
+    work();
+    for (std::thread& th : pool) th.join();
+    if (failed) return false;
+    for (int32_t b = 0; b < P.bins; ++b) {
+        P.max_nodes = std::max(P.max_nodes, bin_nodes[b]);
+        P.max_ranks = std::max(P.max_ranks, bin_ranks[b]);
+    }
+    return true;
+}
+
+}  // namespace cfr

@@ -19,6 +19,7 @@
 #include "mlp.hpp"
 #include "kernels.hpp"
 #include "partition.hpp"
+#include "resident.hpp"
 #include "xkernels.hpp"
 #include "xplan.hpp"
 
@@ -38,6 +39,12 @@ struct cfr_solver {
         if (part32) part32->release();
         if (part64) part64->release();
     }
+    // small game: whole iterations in one launch (the one of the solver's precision is set up)
+    cfr::Resident<float> res32;
+    cfr::Resident<double> res64;
+    bool resident = false;
+    std::vector<int32_t> res_node, res_rank_node;  // canonical node of its nodes, decision nodes
+    bool resident_values = false;  // the last iteration's node values and reach are the resident ones
     cfr::XDev xdev{};
     int engine = ENGINE_NODE;
     int32_t n_games = 1;       // > 1: a batch (forest); canonical exports are unavailable
@@ -123,6 +130,8 @@ struct Sizes {
     bool packs = false;      // subtree packs (their records are on the device)
     bool fp64 = false;       // values, probabilities and state in double precision
     int32_t players = 0;     // general-sum game of n rational players (node engine), else 0
+    bool level_pure = true;
+    bool resident = false;   // small game: the resident iteration's records and state as well
     // node engine: regret contributions may be stored per child and gathered per infoset (false:
     // always added by atomics, for the partitioned iteration's windows)
     bool gather = true;
@@ -148,10 +157,59 @@ int choose_engine(bool level_pure, int32_t max_actions, uint32_t flags) {
     return ENGINE_BLOCK;
 }
 
+cfr::ResSizes resident_sizes(const Sizes& z) {
+    cfr::ResSizes r;
+    r.nodes = z.N; r.decision = z.N - z.terminals; r.members = z.M; r.infosets = z.Hp;
+    r.pairs = z.Qp; r.chance_pairs = z.Q0; r.depth = z.D; r.max_actions = z.max_actions;
+    r.players = z.players; r.real_bytes = z.fp64 ? 8 : 4; r.level_pure = z.level_pure;
+    return r;
+}
+
+// Whether a single game may run resident: its sizes allow it and the configuration asks for none of
+// the level-by-level launches (direct launches, subtree packs, or for a two-player game the node
+// engine by name).
+bool choose_resident(const Sizes& z, uint32_t flags) {
+    if (flags & (CFR_FLAG_NO_GRAPH | CFR_FLAG_SUBTREE_PACKS | CFR_FLAG_KEEP_NODE_VALUES)) return false;
+    if (z.players == 0 && (flags & CFR_FLAG_NODE_ENGINE)) return false;
+    return cfr::resident_fits(resident_sizes(z));
+}
+
+// The resident iteration's arrays, after the engine's.
+template <class F>
+void carve_resident(Carve& c, cfr::Resident<F>& r, const cfr::DevT<F>& d, const Sizes& z) {
+    r = cfr::Resident<F>{};
+    if (!z.resident) return;
+    const int64_t nd = z.N - z.terminals;
+    const int64_t cols = z.players > 0 ? z.players : 1, planes = z.players > 0 ? z.players : 2;
+    const cfr::ResSizes rz = resident_sizes(z);
+    const int64_t roots = cfr::resident_max_roots(rz);
+    r.N = z.N; r.ND = static_cast<int32_t>(nd); r.Hp = static_cast<int32_t>(z.Hp);
+    r.Qp = static_cast<int32_t>(z.Qp); r.Q0 = static_cast<int32_t>(z.Q0); r.D = z.D;
+    r.players = z.players;
+    r.rec = c.take<cfr::Rec4>(nd);
+    r.slot = c.take<int32_t>(nd);
+    r.reach_c = c.take<F>(nd);
+    r.sets = c.take<cfr::Rec4>(z.Hp);
+    r.root_rank = c.take<int32_t>(roots);
+    r.ext = c.take<int32_t>(roots);
+    r.path = c.take<int32_t>(cfr::resident_max_path(rz));
+    r.table = c.take<cfr::Rec4>(cfr::resident_max_table(rz));
+    r.con = c.take<F>(z.M * cfr::res_stride(z.max_actions, sizeof(F)));
+    r.root_val = c.take<F>(cols * roots);
+    r.pay = c.take<F>(cols * (z.N + roots));
+    r.val = c.take<F>(cols * (z.N + roots));
+    r.reach = c.take<F>(planes * nd);
+    r.team = c.take<cfr::ResTeam>(1);
+    r.prob = d.prob; r.R = d.R; r.S = d.S; r.T = d.T;
+}
+
 // Lays out every device array; with base = nullptr it only measures. Canonical layout
 // arrays are always present (they are exported); per-iteration state follows the engine.
-size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes& z) {
+size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes& z,
+             cfr::Resident<float>* r32 = nullptr, cfr::Resident<double>* r64 = nullptr) {
     Carve c(base);
+    cfr::Resident<float> no32;
+    cfr::Resident<double> no64;
     const int64_t N = z.N, Hp = z.Hp, Qp = z.Qp, H0 = z.H0, Q0 = z.Q0, M = z.M;
     const int32_t D = z.D;
     d = cfr::Dev{};
@@ -220,6 +278,7 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         if (store) d64.contrib = c.take<double>(n_contrib);
         d64.pibar = c.take<double>(Hp);
         x = cfr::XDev{};
+        carve_resident(c, r64 != nullptr ? *r64 : no64, d64, z);
         return (c.off + 255) & ~size_t{255};
     }
     d.payoff = c.take<float>(cols * N);
@@ -287,6 +346,7 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         d.sq_offset = x.q_offset;
         d.sq_input = x.q_input;
     }
+    carve_resident(c, r32 != nullptr ? *r32 : no32, d, z);
     return (c.off + 255) & ~size_t{255};
 }
 
@@ -466,6 +526,8 @@ int plan_impl(const cfr_game* game, const cfr_config* config, int32_t players,
               (config->flags & CFR_FLAG_SUBTREE_PACKS) != 0;
     z.fp64 = config != nullptr && (config->flags & CFR_FLAG_FP64) != 0;
     z.players = players;
+    z.level_pure = L.level_pure;
+    z.resident = choose_resident(z, config ? config->flags : 0u);
     cfr::Dev d{};
     cfr::Dev64 d64{};
     cfr::XDev x{};
@@ -761,6 +823,22 @@ void member_slots(const cfr::Layout& L, std::vector<int32_t>& node_slot,
     slot_base[L.Hp] = static_cast<int32_t>(at);
 }
 
+// Copies a resident plan to the device and sets the launch shape.
+template <class F>
+int upload_resident(cfr::Resident<F>& r, const cfr::ResPlan& p, const std::vector<F>& reach_c,
+                    const std::vector<F>& pay, hipStream_t st) {
+    int rc;
+    if ((rc = upload(r.rec, p.rec, st)) || (rc = upload(r.slot, p.slot, st)) ||
+        (rc = upload(r.reach_c, reach_c, st)) || (rc = upload(r.sets, p.sets, st)) ||
+        (rc = upload(r.root_rank, p.root_rank, st)) || (rc = upload(r.ext, p.ext, st)) ||
+        (rc = upload(r.path, p.path, st)) || (rc = upload(r.table, p.table, st)) ||
+        (rc = upload(r.pay, pay, st)))
+        return rc;
+    cfr::resident_shape(r, p);
+    cfr::launch_resident_reset(r, st);
+    return CFR_OK;
+}
+
 // cfr_build for a two-player zero-sum game (players = 0) or a general-sum game of `players`
 // with its payoff matrix (the node engine; simultaneous or, alternating, a pass per player).
 int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, const double* payoff,
@@ -783,6 +861,8 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     z.packs = z.engine == ENGINE_BLOCK && L.max_actions <= 4 && (cfg.flags & CFR_FLAG_SUBTREE_PACKS);
     z.fp64 = fp64;
     z.players = players;
+    z.level_pure = L.level_pure;
+    z.resident = choose_resident(z, cfg.flags);
     cfr::ExecPlan P;
     if (z.engine == ENGINE_BLOCK) {
         // subtree packs are instantiated for at most 4 actions per infoset
@@ -797,12 +877,12 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     if (bytes < need)
         return set_err(CFR_ENOMEM, "workspace has " + std::to_string(bytes) + " bytes, needs " +
                                        std::to_string(need));
-    carve(d, d64, x, workspace, z);
-
     auto* s = new cfr_solver();
+    carve(d, d64, x, workspace, z, &s->res32, &s->res64);
     s->dev = d;
     s->dev64 = d64;
     s->fp64 = fp64;
+    s->resident = z.resident;
     s->xdev = x;
     s->engine = z.engine;
     s->rule = rule_of(cfg);
@@ -874,6 +954,35 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     if (fp64) cfr::launch_reset(d64, st, true);
     else cfr::launch_reset(d, st, s->engine == ENGINE_NODE);
     if (s->engine == ENGINE_BLOCK) cfr::launch_x_reset(s->xdev, st);
+    cfr::ResPlan rp;
+    std::vector<float> reach_c32, res_pay32;
+    std::vector<double> res_pay64;
+    if (s->resident) {
+        std::vector<int32_t> q_of(L.q_offset.begin(), L.q_offset.begin() + L.Hp);
+        if (s->engine == ENGINE_BLOCK)
+            for (int64_t e = 0; e < L.Hp; ++e) q_of[P.infoset_canon[e]] = P.q_offset[e];
+        s->resident = cfr::build_resident(L, q_of, resident_sizes(z), rp);
+    }
+    if (s->resident) {
+        if (!fp64) reach_c32.assign(rp.reach_c.begin(), rp.reach_c.end());
+        // payoffs in the bins' order
+        const auto in_bins = [&](const auto& pay, auto& out) {
+            const int64_t nb = static_cast<int64_t>(rp.node.size()), cols = players > 0 ? players : 1;
+            out.resize(cols * nb);
+            for (int64_t c = 0; c < cols; ++c)
+                for (int64_t i = 0; i < nb; ++i) out[c * nb + i] = pay[c * L.N + rp.node[i]];
+        };
+        if (fp64) in_bins(players > 0 ? pay64 : L.payoff64, res_pay64);
+        else in_bins(players > 0 ? pay32 : L.payoff, res_pay32);
+        rc = fp64 ? upload_resident(s->res64, rp, rp.reach_c, res_pay64, st)
+                  : upload_resident(s->res32, rp, reach_c32, res_pay32, st);
+        if (rc != CFR_OK) {
+            discard(s);
+            return rc;
+        }
+        s->res_node = rp.node;
+        s->res_rank_node = rp.rank_node;
+    }
     if ((rc = check_hip("reset")) != CFR_OK) {
         discard(s);
         return rc;
@@ -884,7 +993,8 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
         discard(s);
         return hip_err(e, "build synchronise");
     }
-    if (s->use_graph && (rc = capture(s)) != CFR_OK) {
+    // (a resident game's iterations need no graph)
+    if (s->use_graph && !s->resident && (rc = capture(s)) != CFR_OK) {
         discard(s);
         return rc;
     }
@@ -1109,6 +1219,14 @@ int cfr_build_partitioned(const cfr_game* game, const cfr_config* config, int32_
 
 int cfr_iterate(cfr_solver* s, int32_t n) {
     if (s == nullptr || n < 0) return set_err(CFR_EINVAL, "bad solver or count");
+    if (s->resident && n > 0) {
+        if (s->fp64) cfr::launch_resident(s->res64, s->rule, s->alternating, n, s->stream);
+        else cfr::launch_resident(s->res32, s->rule, s->alternating, n, s->stream);
+        if (const int rc = check_hip("iteration launch"); rc != CFR_OK) return rc;
+        s->resident_values = true;
+        s->T += n;
+        return CFR_OK;
+    }
     for (int32_t i = 0; i < n; ++i) {
         if (s->use_graph) {
             HIP_TRY(hipGraphLaunch(s->exec, s->stream), "graph launch");
@@ -1171,6 +1289,7 @@ int cfr_iterate_timed(cfr_solver* s, int32_t n, double* kernel_ms, int64_t* kern
         kernel_launches[k] = 0;
     }
     EventTimer timer;
+    s->resident_values = s->resident_values && n == 0;
     for (int32_t i = 0; i < n; ++i) {
         timer.used = 0;
         timer.kinds.clear();
@@ -1201,6 +1320,7 @@ int cfr_iterate_profile(cfr_solver* s, int32_t n, double* launch_ms, int32_t* la
     if (s == nullptr || n < 1 || n_launches == nullptr || max_launches < 0)
         return set_err(CFR_EINVAL, "bad argument");
     EventTimer timer;
+    s->resident_values = false;
     std::vector<double> acc;
     for (int32_t i = 0; i < n; ++i) {
         timer.used = 0;
@@ -1265,7 +1385,7 @@ int cfr_set_launch_shape(cfr_solver* s, const cfr_launch_shape* shape) {
     if (s->graph != nullptr) (void)hipGraphDestroy(s->graph);
     s->exec = nullptr;
     s->graph = nullptr;
-    if (s->use_graph) return capture(s);
+    if (s->use_graph && !s->resident) return capture(s);
     return CFR_OK;
 }
 
@@ -1514,9 +1634,43 @@ int cfr_get_layout(cfr_solver* s, const char* name, void* out, int64_t bytes) {
 
 namespace {
 
+// The node values and reach of a resident game's last iteration, in canonical order: columns at
+// value[c N + v]; planes at planes[k N + v] (the players', then chance's; 0 at terminal nodes,
+// which have none).
+template <class F>
+int resident_values(cfr_solver* s, const cfr::Resident<F>& r, std::vector<F>* value,
+                    std::vector<F>* planes) {
+    const int64_t N = r.N, nd = r.ND, cols = r.players > 0 ? r.players : 1,
+                  np = r.players > 0 ? r.players : 2;
+    std::vector<F> reach(planes != nullptr ? (np + 1) * nd : 0);
+    const int64_t nb = r.NB;
+    std::vector<F> val(value != nullptr ? cols * nb : 0);
+    if (value != nullptr)
+        HIP_TRY(hipMemcpyAsync(val.data(), r.val, cols * nb * sizeof(F), hipMemcpyDeviceToHost,
+                               s->stream), "value copy");
+    if (planes != nullptr) {
+        HIP_TRY(hipMemcpyAsync(reach.data(), r.reach, np * nd * sizeof(F), hipMemcpyDeviceToHost,
+                               s->stream), "reach copy");
+        HIP_TRY(hipMemcpyAsync(reach.data() + np * nd, r.reach_c, nd * sizeof(F),
+                               hipMemcpyDeviceToHost, s->stream), "reach copy");
+    }
+    HIP_TRY(hipStreamSynchronize(s->stream), "node values synchronise");
+    if (value != nullptr) {
+        value->resize(cols * N);
+        for (int64_t c = 0; c < cols; ++c)
+            for (int64_t i = 0; i < nb; ++i) (*value)[c * N + s->res_node[i]] = val[c * nb + i];
+    }
+    if (planes != nullptr) {
+        planes->assign((np + 1) * N, F(0));
+        for (int64_t k = 0; k <= np; ++k)
+            for (int64_t d = 0; d < nd; ++d) (*planes)[k * N + s->res_rank_node[d]] = reach[k * nd + d];
+    }
+    return CFR_OK;
+}
+
 template <class F>
 int node_values_t(cfr_solver* s, const F* value, const F* reach_planes, F* u1, F* reach,
-                  int64_t n_nodes) {
+                  int64_t n_nodes, const cfr::Resident<F>& res) {
     if (!s->canonical) return set_err(CFR_EINVAL, "node values are not exported for a batch");
     if (n_nodes != s->dev.N) return set_err(CFR_EINVAL, "n_nodes does not match the game");
     if (s->engine == ENGINE_BLOCK && s->xdev.n_tiers > 0 && !s->keep_nodes)
@@ -1524,6 +1678,16 @@ int node_values_t(cfr_solver* s, const F* value, const F* reach_planes, F* u1, F
                                    "CFR_FLAG_KEEP_NODE_VALUES to read them");
     const int64_t N = s->dev.N;
     std::vector<F> val(u1 != nullptr ? N : 0), planes(reach != nullptr ? 3 * N : 0);
+    if (s->resident_values) {
+        if (const int rc = resident_values(s, res, u1 != nullptr ? &val : nullptr,
+                                           reach != nullptr ? &planes : nullptr); rc != CFR_OK)
+            return rc;
+        if (u1 != nullptr) std::copy(val.begin(), val.end(), u1);
+        if (reach != nullptr)
+            for (int64_t v = 0; v < N; ++v)
+                for (int k = 0; k < 3; ++k) reach[3 * v + k] = planes[k * N + v];
+        return CFR_OK;
+    }
     std::vector<int32_t> canon(s->engine == ENGINE_BLOCK ? N : 0);
     if (u1 != nullptr)
         HIP_TRY(hipMemcpyAsync(val.data(), value, N * sizeof(F), hipMemcpyDeviceToHost,
@@ -1544,6 +1708,17 @@ int node_values_t(cfr_solver* s, const F* value, const F* reach_planes, F* u1, F
     return CFR_OK;
 }
 
+// Columns val[i N + v] and planes[k N + v] of a game of P players, node-major (null: skipped).
+void values_out(const std::vector<double>& val, const std::vector<double>& planes, double* values,
+                double* reach, int64_t N, int64_t P) {
+    for (int64_t v = 0; v < N; ++v) {
+        if (values != nullptr)
+            for (int64_t i = 0; i < P; ++i) values[v * P + i] = val[i * N + v];
+        if (reach != nullptr)
+            for (int64_t k = 0; k <= P; ++k) reach[v * (P + 1) + k] = planes[k * N + v];
+    }
+}
+
 }  // namespace
 
 extern "C" {
@@ -1552,14 +1727,14 @@ int cfr_get_node_values(cfr_solver* s, float* u1, float* reach, int64_t n_nodes)
     if (s == nullptr) return set_err(CFR_EINVAL, "null solver");
     if (s->players > 0) return set_err(CFR_EINVAL, "a general-sum solver: use cfr_get_node_values_n");
     if (const int rc = check_precision(s, false); rc != CFR_OK) return rc;
-    return node_values_t(s, s->dev.value, s->dev.reach, u1, reach, n_nodes);
+    return node_values_t(s, s->dev.value, s->dev.reach, u1, reach, n_nodes, s->res32);
 }
 
 int cfr_get_node_values_f64(cfr_solver* s, double* u1, double* reach, int64_t n_nodes) {
     if (s == nullptr) return set_err(CFR_EINVAL, "null solver");
     if (s->players > 0) return set_err(CFR_EINVAL, "a general-sum solver: use cfr_get_node_values_n");
     if (const int rc = check_precision(s, true); rc != CFR_OK) return rc;
-    return node_values_t(s, s->dev64.value, s->dev64.reach, u1, reach, n_nodes);
+    return node_values_t(s, s->dev64.value, s->dev64.reach, u1, reach, n_nodes, s->res64);
 }
 
 int cfr_get_node_values_n(cfr_solver* s, double* values, double* reach, int64_t n_nodes) {
@@ -1584,6 +1759,20 @@ int cfr_get_node_values_n(cfr_solver* s, double* values, double* reach, int64_t 
         return CFR_OK;
     };
     int rc;
+    if (s->resident_values) {
+        auto widen = [&](const auto& r, auto F0) -> int {
+            std::vector<decltype(F0)> v, p;
+            if (const int e = resident_values(s, r, values != nullptr ? &v : nullptr,
+                                              reach != nullptr ? &p : nullptr); e != CFR_OK)
+                return e;
+            val.assign(v.begin(), v.end());
+            planes.assign(p.begin(), p.end());
+            return CFR_OK;
+        };
+        if ((rc = s->fp64 ? widen(s->res64, 0.0) : widen(s->res32, 0.0f)) != CFR_OK) return rc;
+        values_out(val, planes, values, reach, N, P);
+        return CFR_OK;
+    }
     if (values != nullptr &&
         (rc = fetch(s->dev.value, s->dev64.value, val, P * N, "value copy")) != CFR_OK)
         return rc;
@@ -1591,12 +1780,7 @@ int cfr_get_node_values_n(cfr_solver* s, double* values, double* reach, int64_t 
         (rc = fetch(s->dev.reach, s->dev64.reach, planes, (P + 1) * N, "reach copy")) != CFR_OK)
         return rc;
     HIP_TRY(hipStreamSynchronize(s->stream), "node values synchronise");
-    for (int64_t v = 0; v < N; ++v) {
-        if (values != nullptr)
-            for (int64_t i = 0; i < P; ++i) values[v * P + i] = val[i * N + v];
-        if (reach != nullptr)
-            for (int64_t k = 0; k <= P; ++k) reach[v * (P + 1) + k] = planes[k * N + v];
-    }
+    values_out(val, planes, values, reach, N, P);
     return CFR_OK;
 }
 
