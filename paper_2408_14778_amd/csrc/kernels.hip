@@ -25,6 +25,10 @@ inline unsigned blocks_for(int64_t n) {
     return static_cast<unsigned>((n + kBlock - 1) / kBlock);
 }
 
+inline unsigned blocks_of(int64_t n, int threads) {
+    return static_cast<unsigned>((n + threads - 1) / threads);
+}
+
 __device__ __forceinline__ int64_t gid() {
     return static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
 }
@@ -495,21 +499,28 @@ __global__ void k_average(int64_t Hp, const int32_t* __restrict__ q_offset,
     }
 }
 
-// ---- best response (Section 2.2): the responder i maximises, everyone else plays avgprob
+// ---- best response (Section 2.2): the responder i maximises, everyone else plays avgprob. Both
+// players in one sweep: br_reach[p N + v] = pi_{-i}(v) for i = p + 1, br_value[p N + v] = the value
+// of v to player i when i best responds. Terminal entries of br_value (+u_1, -u_1) and the root's
+// reach are written when the solver is set up and never again.
 
 template <class F>
-__global__ void k_br_terminal(int64_t N, const int8_t* __restrict__ node_player,
-                              const F* __restrict__ payoff, F sgn, F* __restrict__ br_value,
-                              F* __restrict__ br_reach) {
+__global__ void k_br_setup(int64_t N, const int8_t* __restrict__ node_player,
+                           const F* __restrict__ payoff, F* __restrict__ br_value,
+                           F* __restrict__ br_reach) {
     const int64_t v = gid();
     if (v >= N) return;
-    br_value[v] = node_player[v] < 0 ? sgn * payoff[v] : F(0);
-    if (v == 0) br_reach[0] = F(1);
+    if (node_player[v] < 0) {
+        br_value[v] = payoff[v];
+        br_value[N + v] = -payoff[v];
+    }
+    if (v == 0) br_reach[0] = br_reach[N] = F(1);
 }
 
-// pi_{-i}: product of chance and opponent edge probabilities (decision nodes only).
+// One level from its parents' reach: chance and player-2 edges for pi_{-1}, chance and player-1
+// edges for pi_{-2} (decision nodes only).
 template <class F>
-__global__ void k_br_reach_level(int32_t lo, int32_t hi, int player,
+__global__ void k_br_reach_level(int32_t lo, int32_t hi, int64_t N,
                                  const int32_t* __restrict__ parent,
                                  const int8_t* __restrict__ node_player,
                                  const int32_t* __restrict__ node_edge,
@@ -518,13 +529,41 @@ __global__ void k_br_reach_level(int32_t lo, int32_t hi, int player,
     if (v >= hi) return;
     if (node_player[v] < 0) return;
     const int32_t p = parent[v];
-    const F f = node_player[p] == player ? F(1) : avgprob[node_edge[v]];
-    br_reach[v] = br_reach[p] * f;
+    const F s = avgprob[node_edge[v]];
+    const int8_t who = node_player[p];
+    const F r0 = br_reach[p], r1 = br_reach[N + p];
+    br_reach[v] = who == 1 ? r0 : r0 * s;
+    br_reach[N + v] = who == 2 ? r1 : r1 * s;
 }
 
-// a*(h) = argmax_a sum_{d in h} pi_{-i}(d) V(child(d, a)), lowest index on ties.
+// Every level in one launch: each decision node walks up to the root and multiplies the edges on its
+// path. The walk repeats what the levels share, but costs one launch (about 0.3 us per step)
+// instead of one of 3 to 4 us per level.
 template <class F>
-__global__ void k_br_choose(int32_t hlo, int32_t hhi, int player,
+__global__ void k_br_reach_path(int64_t n, int64_t N, const int32_t* __restrict__ parent,
+                                const int8_t* __restrict__ node_player,
+                                const int32_t* __restrict__ node_edge,
+                                const F* __restrict__ avgprob, F* __restrict__ br_reach) {
+    const int64_t v = 1 + gid();
+    if (v >= n || node_player[v] < 0) return;
+    F r0 = F(1), r1 = F(1);
+    for (int32_t y = static_cast<int32_t>(v); y > 0;) {
+        const int32_t p = parent[y];
+        const F s = avgprob[node_edge[y]];
+        const int8_t who = node_player[p];
+        if (who != 1) r0 *= s;
+        if (who != 2) r1 *= s;
+        y = p;
+    }
+    br_reach[v] = r0;
+    br_reach[N + v] = r1;
+}
+
+// a*(h) = argmax_a sum_{d in h} pi_{-i}(d) V_i(child(d, a)), lowest index on ties: one thread per
+// infoset, kGatherActions actions per walk over its members, four members' loads at a time (each
+// action's sum in member order).
+template <class F>
+__global__ void k_br_choose(int32_t hlo, int32_t hhi, int64_t N,
                             const int8_t* __restrict__ infoset_player,
                             const int32_t* __restrict__ q_offset,
                             const int32_t* __restrict__ member_offset,
@@ -532,29 +571,51 @@ __global__ void k_br_choose(int32_t hlo, int32_t hhi, int player,
                             const int32_t* __restrict__ child_begin,
                             const F* __restrict__ br_reach, const F* __restrict__ br_value,
                             int32_t* __restrict__ best) {
+    constexpr int KB = kGatherActions, MB = 4;
     const int64_t h = hlo + gid();
     if (h >= hhi) return;
-    if (infoset_player[h] != player) return;
+    const int64_t plane = static_cast<int64_t>(infoset_player[h] - 1) * N;
     const int32_t k = q_offset[h + 1] - q_offset[h];
     const int32_t m0 = member_offset[h], m1 = member_offset[h + 1];
     int32_t a_star = 0;
     F v_star = F(0);
-    for (int32_t a = 0; a < k; ++a) {
-        F tot = F(0);
-        for (int32_t m = m0; m < m1; ++m) {
-            const int32_t d = members[m];
-            tot = fma_(br_reach[d], br_value[child_begin[d] + a], tot);
+    for (int32_t a0 = 0; a0 < k; a0 += KB) {
+        F tot[KB];
+#pragma unroll
+        for (int j = 0; j < KB; ++j) tot[j] = F(0);
+        for (int32_t mb = m0; mb < m1; mb += MB) {
+            int32_t d[MB], cb[MB];
+            F r[MB], v[MB][KB];
+            // (past the last member or action: repeated, unused)
+#pragma unroll
+            for (int u = 0; u < MB; ++u) d[u] = members[min(mb + u, m1 - 1)];
+#pragma unroll
+            for (int u = 0; u < MB; ++u) {
+                cb[u] = child_begin[d[u]];
+                r[u] = br_reach[plane + d[u]];
+            }
+#pragma unroll
+            for (int u = 0; u < MB; ++u)
+#pragma unroll
+                for (int j = 0; j < KB; ++j) v[u][j] = br_value[plane + cb[u] + min(a0 + j, k - 1)];
+#pragma unroll
+            for (int u = 0; u < MB; ++u)
+                if (mb + u < m1)
+#pragma unroll
+                    for (int j = 0; j < KB; ++j) tot[j] = fma_(r[u], v[u][j], tot[j]);
         }
-        if (a == 0 || tot > v_star) {
-            v_star = tot;
-            a_star = a;
-        }
+#pragma unroll
+        for (int j = 0; j < KB; ++j)
+            if (a0 + j < k && (a0 + j == 0 || tot[j] > v_star)) {
+                v_star = tot[j];
+                a_star = a0 + j;
+            }
     }
     best[h] = a_star;
 }
 
 template <class F>
-__global__ void k_br_value_level(int32_t lo, int32_t hi, int player,
+__global__ void k_br_value_level(int32_t lo, int32_t hi, int64_t N,
                                  const int32_t* __restrict__ child_begin,
                                  const int8_t* __restrict__ node_player,
                                  const int32_t* __restrict__ node_infoset,
@@ -566,18 +627,58 @@ __global__ void k_br_value_level(int32_t lo, int32_t hi, int player,
     const int8_t who = node_player[p];
     if (who < 0) return;
     const int32_t c0 = child_begin[p], c1 = child_begin[p + 1];
-    if (who == player) {
-        br_value[p] = br_value[c0 + best[node_infoset[p]]];
-        return;
+    // the acting player's column takes the best child's, the others the expectation
+    const int32_t pick = who > 0 ? c0 + best[node_infoset[p]] : c0;
+    F u0 = F(0), u1 = F(0);
+#pragma unroll 4
+    for (int32_t c = c0; c < c1; ++c) {
+        const F s = avgprob[node_edge[c]];
+        u0 = fma_(s, br_value[c], u0);
+        u1 = fma_(s, br_value[N + c], u1);
     }
-    F u = F(0);
-    for (int32_t c = c0; c < c1; ++c) u = fma_(avgprob[node_edge[c]], br_value[c], u);
-    br_value[p] = u;
+    br_value[p] = who == 1 ? br_value[pick] : u0;
+    br_value[N + p] = who == 2 ? br_value[N + pick] : u1;
+}
+
+// k_br_value_level for a level of few nodes: a wavefront per node, lanes over its children, a
+// fixed butterfly (a root dealing many private types would otherwise walk them on one thread).
+template <class F>
+__global__ void __launch_bounds__(256) k_br_value_wide(int32_t lo, int32_t hi, int64_t N,
+                                                       const int32_t* __restrict__ child_begin,
+                                                       const int8_t* __restrict__ node_player,
+                                                       const int32_t* __restrict__ node_infoset,
+                                                       const int32_t* __restrict__ node_edge,
+                                                       const F* __restrict__ avgprob,
+                                                       const int32_t* __restrict__ best,
+                                                       F* __restrict__ br_value) {
+    const int lane = threadIdx.x & 63;
+    const int64_t p = lo + (gid() >> 6);
+    if (p >= hi) return;  // whole wavefronts leave together
+    const int8_t who = node_player[p];
+    if (who < 0) return;
+    const int32_t c0 = child_begin[p], c1 = child_begin[p + 1];
+    F u0 = F(0), u1 = F(0);
+#pragma unroll 4
+    for (int32_t c = c0 + lane; c < c1; c += 64) {
+        const F s = avgprob[node_edge[c]];
+        u0 = fma_(s, br_value[c], u0);
+        u1 = fma_(s, br_value[N + c], u1);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        u0 += __shfl_xor(u0, off, 64);
+        u1 += __shfl_xor(u1, off, 64);
+    }
+    if (lane == 0) {
+        const int32_t pick = who > 0 ? c0 + best[node_infoset[p]] : c0;
+        br_value[p] = who == 1 ? br_value[pick] : u0;
+        br_value[N + p] = who == 2 ? br_value[N + pick] : u1;
+    }
 }
 
 template <class F>
-__global__ void k_br_store(const F* __restrict__ br_value, double* out) {
-    if (gid() == 0) *out = static_cast<double>(br_value[0]);
+__global__ void k_br_store(int64_t N, const F* __restrict__ br_value, double* out) {
+    const int64_t i = gid();
+    if (i < 2) out[i] = static_cast<double>(br_value[i * N]);
 }
 
 template <class F>
@@ -609,6 +710,9 @@ void launch_reset(const DevT<F>& d, hipStream_t st, bool node_arrays) {
     else if (node_arrays)
         hipLaunchKernelGGL(k_reset_nodes<F>, dim3(blocks_for(d.N)), dim3(kBlock), 0, st, d.N,
                            d.node_player, d.payoff, d.value, d.reach);
+    if (node_arrays && d.br_value != nullptr)
+        hipLaunchKernelGGL(k_br_setup<F>, dim3(blocks_for(d.N)), dim3(kBlock), 0, st, d.N,
+                           d.node_player, d.payoff, d.br_value, d.br_reach);
     if (d.Q0 > 0)
         hipLaunchKernelGGL(k_copy_tail<F>, dim3(blocks_for(d.Q0)), dim3(kBlock), 0, st, d.Q0,
                            d.prob + d.Qp, d.avgprob + d.Qp);
@@ -753,30 +857,33 @@ void launch_average(const DevT<F>& d, hipStream_t st) {
 }
 
 template <class F>
-void launch_best_response(const DevT<F>& d, const int32_t* lo, const int32_t* hlo, int player,
-                          hipStream_t st) {
-    const F sgn = player == 1 ? F(1) : F(-1);
-    hipLaunchKernelGGL(k_br_terminal<F>, dim3(blocks_for(d.N)), dim3(kBlock), 0, st, d.N,
-                       d.node_player, d.payoff, sgn, d.br_value, d.br_reach);
-    for (int32_t l = 1; l < d.D; ++l) {
-        const int32_t a = lo[l], b = lo[l + 1];
-        hipLaunchKernelGGL(k_br_reach_level<F>, dim3(blocks_for(b - a)), dim3(kBlock), 0, st, a,
-                           b, player, d.parent, d.node_player, d.node_edge, d.avgprob,
+void launch_best_response(const DevT<F>& d, const int32_t* lo, const int32_t* hlo, hipStream_t st) {
+    if (d.D > 1 && br_path_applies(d.N, d.D)) {
+        hipLaunchKernelGGL(k_br_reach_path<F>, dim3(blocks_for(lo[d.D])), dim3(kBlock), 0, st,
+                           int64_t{lo[d.D]}, d.N, d.parent, d.node_player, d.node_edge, d.avgprob,
                            d.br_reach);
+    } else {
+        for (int32_t l = 1; l < d.D; ++l)
+            hipLaunchKernelGGL(k_br_reach_level<F>, dim3(blocks_for(lo[l + 1] - lo[l])), dim3(kBlock), 0,
+                               st, lo[l], lo[l + 1], d.N, d.parent, d.node_player, d.node_edge,
+                               d.avgprob, d.br_reach);
     }
     for (int32_t l = d.D - 1; l >= 0; --l) {
         const int32_t ha = hlo[l], hb = hlo[l + 1];
         if (hb > ha)
-            hipLaunchKernelGGL(k_br_choose<F>, dim3(blocks_for(hb - ha)), dim3(kBlock), 0, st, ha,
-                               hb, player, d.infoset_player, d.q_offset, d.member_offset,
-                               d.members, d.child_begin, d.br_reach, d.br_value, d.best);
+            hipLaunchKernelGGL(k_br_choose<F>, dim3(blocks_of(hb - ha, 64)), dim3(64), 0, st, ha, hb,
+                               d.N, d.infoset_player, d.q_offset, d.member_offset, d.members,
+                               d.child_begin, d.br_reach, d.br_value, d.best);
         const int32_t a = lo[l], b = lo[l + 1];
-        hipLaunchKernelGGL(k_br_value_level<F>, dim3(blocks_for(b - a)), dim3(kBlock), 0, st, a,
-                           b, player, d.child_begin, d.node_player, d.node_infoset, d.node_edge,
-                           d.avgprob, d.best, d.br_value);
+        auto value = [&](auto kernel, unsigned grid) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, st, a, b, d.N, d.child_begin,
+                               d.node_player, d.node_infoset, d.node_edge, d.avgprob, d.best,
+                               d.br_value);
+        };
+        if (b - a <= kWideNodes) value(k_br_value_wide<F>, blocks_for(int64_t{64} * (b - a)));
+        else value(k_br_value_level<F>, blocks_for(b - a));
     }
-    hipLaunchKernelGGL(k_br_store<F>, dim3(1), dim3(64), 0, st, d.br_value,
-                       d.out2 + (player - 1));
+    hipLaunchKernelGGL(k_br_store<F>, dim3(1), dim3(64), 0, st, d.N, d.br_value, d.out2);
 }
 
 template <class F>
@@ -803,7 +910,7 @@ void launch_gather_q(const DevT<F>& d, const F* src, F* dst, hipStream_t st) {
     template void launch_reach_range<F>(const DevT<F>&, int32_t, int32_t, hipStream_t);        \
     template void launch_value_range<F>(const DevT<F>&, int32_t, int32_t, hipStream_t);        \
     template void launch_infoset_pass<F>(const DevT<F>&, const UpdateRule&, hipStream_t);      \
-    template void launch_best_response<F>(const DevT<F>&, const int32_t*, const int32_t*, int, \
+    template void launch_best_response<F>(const DevT<F>&, const int32_t*, const int32_t*,      \
                                           hipStream_t);                                        \
     template void launch_scatter_q<F>(const DevT<F>&, const F*, F*, hipStream_t);              \
     template void launch_gather_q<F>(const DevT<F>&, const F*, F*, hipStream_t);

@@ -64,8 +64,8 @@ struct DevT {
     int64_t* T;             // iterations done (device copy)
     // exploitability and staging
     F* avgprob;             // Qp + Q0: average strategy, then sigma_0
-    F* br_reach;            // N
-    F* br_value;            // N
+    F* br_reach;            // 2N: pi_{-1}, pi_{-2} (null: general-sum and partitioned solvers)
+    F* br_value;            // 2N: values under player 1's, player 2's best response
     int32_t* best;          // Hp
     F* stage;               // 2 * Qp (state and average-strategy transfers)
     double* out2;           // 2 best-response values
@@ -151,10 +151,14 @@ void launch_infoset_pass(const DevT<F>& d, const UpdateRule& rule, hipStream_t s
 // Average strategy into d.avgprob (canonical order; chance tail copied at reset).
 template <class F>
 void launch_average(const DevT<F>& d, hipStream_t st);
-// Best response of player i against d.avgprob; value lands in d.out2[i - 1].
+// Best responses of both players against d.avgprob; player i's value lands in d.out2[i - 1].
 template <class F>
 void launch_best_response(const DevT<F>& d, const int32_t* level_offset_host,
-                          const int32_t* infoset_level_offset_host, int player, hipStream_t st);
+                          const int32_t* infoset_level_offset_host, hipStream_t st);
+// Whether a best response takes every level's reach in one launch of walks to the root (measured per
+// check: 2.6 million nodes of 15 levels 17 us against 49 us in 14 launches). The walks' work grows
+// with nodes times depth, the launches they replace with the depth alone.
+inline bool br_path_applies(int64_t nodes, int32_t depth) { return nodes <= 4000000 && depth <= 24; }
 // dst[q_input[q]] = src[q]  (canonical -> input order)
 template <class F>
 void launch_scatter_q(const DevT<F>& d, const F* src, F* dst, hipStream_t st);

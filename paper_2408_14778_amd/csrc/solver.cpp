@@ -271,8 +271,10 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         d64.value = c.take<double>(cols * N);
         d64.reach = c.take<double>(planes * N);
         d64.avgprob = c.take<double>(Qp + Q0);
-        d64.br_reach = c.take<double>(N);
-        d64.br_value = c.take<double>(N);
+        if (z.players == 0 && z.gather) {  // (others have no best response)
+            d64.br_reach = c.take<double>(2 * N);
+            d64.br_value = c.take<double>(2 * N);
+        }
         d64.stage = c.take<double>(2 * Qp);
         d64.rtilde = c.take<double>(Qp);
         if (store) d64.contrib = c.take<double>(n_contrib);
@@ -290,8 +292,10 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
     d.T = c.take<int64_t>(1);
     d.avgprob = c.take<float>(Qp + Q0);
     if (z.engine == ENGINE_NODE) {
-        d.br_reach = c.take<float>(N);
-        d.br_value = c.take<float>(N);
+        if (z.players == 0 && z.gather) {  // (others have no best response)
+            d.br_reach = c.take<float>(2 * N);
+            d.br_value = c.take<float>(2 * N);
+        }
         d.best = c.take<int32_t>(Hp);
     }
     d.stage = c.take<float>(2 * Qp);
@@ -1509,17 +1513,15 @@ int cfr_exploitability(cfr_solver* s, double* expl, double br_value[2]) {
     if (!s->level_pure) return set_err(CFR_ELEVEL, "an infoset spans several levels");
     if (s->fp64) {
         cfr::launch_average(s->dev64, s->stream);
-        for (int player = 1; player <= 2; ++player)
-            cfr::launch_best_response(s->dev64, s->level_offset.data(),
-                                      s->infoset_level_offset.data(), player, s->stream);
+        cfr::launch_best_response(s->dev64, s->level_offset.data(), s->infoset_level_offset.data(),
+                                  s->stream);
     } else {
         cfr::launch_average(s->dev, s->stream);
         if (s->engine == ENGINE_BLOCK) {
             cfr::launch_x_best_response(s->xdev, s->dev.avgprob, s->stream);
         } else {
-            for (int player = 1; player <= 2; ++player)
-                cfr::launch_best_response(s->dev, s->level_offset.data(),
-                                          s->infoset_level_offset.data(), player, s->stream);
+            cfr::launch_best_response(s->dev, s->level_offset.data(),
+                                      s->infoset_level_offset.data(), s->stream);
         }
     }
     int rc = check_hip("best response launch");

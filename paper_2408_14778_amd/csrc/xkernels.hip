@@ -1024,6 +1024,29 @@ __global__ void k_x_br_reach(int32_t lo, int32_t hi, int64_t N, const int32_t* _
     }
 }
 
+// Every level in one launch: each decision node of lo .. hi - 1 walks up to its root (nodes below
+// n_roots) and multiplies the edges on its path (br_path_applies says when).
+__global__ void __launch_bounds__(256) k_x_br_reach_path(int32_t lo, int32_t hi, int32_t n_roots,
+                                                         int64_t N,
+                                                         const int32_t* __restrict__ parent,
+                                                         const int32_t* __restrict__ edge,
+                                                         const int8_t* __restrict__ meta,
+                                                         const float* __restrict__ avgprob,
+                                                         float* __restrict__ br_reach) {
+    const int64_t x = lo + gid();
+    if (x >= hi || (meta[x] & 3) == 0) return;
+    float r0 = 1.0f, r1 = 1.0f;
+    for (int32_t y = static_cast<int32_t>(x); y >= n_roots;) {
+        const int actor = meta[y] >> 2;  // 1 chance, 2 player 1, 3 player 2
+        const float s = avgprob[edge[y]];
+        y = parent[y];
+        if (actor != 2) r0 *= s;  // chance or player 2 moved: pi_{-1}
+        if (actor != 3) r1 *= s;  // chance or player 1 moved: pi_{-2}
+    }
+    br_reach[x] = r0;
+    br_reach[N + x] = r1;
+}
+
 struct BrArgs {
     int64_t N;
     const int32_t* chunk_first;
@@ -1568,7 +1591,11 @@ void launch_br_cap(const XDev& x, const BrArgs& a, int32_t l, hipStream_t st) {
 
 void launch_x_best_response(const XDev& x, const float* avgprob, hipStream_t st) {
     const int32_t* lo = x.level_offset_host;
-    for (int32_t l = 1; l < x.D; ++l)
+    if (x.D > 1 && br_path_applies(x.N, x.D))
+        hipLaunchKernelGGL(k_x_br_reach_path, dim3(blocks_of(lo[x.D] - lo[1], kBlock)), dim3(kBlock), 0,
+                           st, lo[1], lo[x.D], lo[1], x.N, x.parent, x.edge, x.meta, avgprob,
+                           x.br_reach);
+    else for (int32_t l = 1; l < x.D; ++l)
         hipLaunchKernelGGL(k_x_br_reach, dim3(blocks_of(lo[l + 1] - lo[l], 2 * kBlock)), dim3(kBlock),
                            0, st, lo[l], lo[l + 1], x.N, x.parent, x.edge, x.meta, avgprob,
                            x.br_reach);
