@@ -345,7 +345,7 @@ def bench_nplayer(args, g) -> dict:
 def bench_partitioned(args, g) -> dict:
     """The large game through the subtree-partitioned, out-of-core iteration (cut at level 8,
     windows of at most 2^21 nodes), CFR+: node-updates/s, and the host link it is bound by:
-    every iteration streams each partition's window (the pinned bytes) host to device."""
+    every iteration reads each partition's records (the pinned bytes) host to device."""
     from paper_2408_14778_amd import PartitionedSolver
 
     s = PartitionedSolver(g, "cfr+", cut_level=8, max_window_nodes=1 << 21,

@@ -276,13 +276,15 @@ int cfr_get_node_values_n(cfr_solver* s, double* values, double* reach, int64_t 
  * proposes: the iteration computed over root-to-leaf partitions of the tree instead of all of it
  * at once). Levels 0 .. cut_level stay resident on the device; the subtrees hanging from the
  * level-cut nodes are grouped, in canonical order, into partitions of at most max_window_nodes
- * nodes below the cut (a larger subtree is a partition of its own), kept in pinned host memory
- * and streamed through one device window every iteration: the resident top-down pass, then per
- * partition its window copied in, its top-down and bottom-up passes (values, regrets and own
- * reaches added into the resident per-pair accumulators) and the bottom-up of its level-cut
- * nodes; the resident bottom-up; the infoset update. The arithmetic is the node engine's (FP32,
- * or FP64 with CFR_FLAG_FP64); device memory holds the resident levels, one window and the
- * per-pair state. cut_level in 1 .. depth - 1, max_window_nodes >= 1 (CFR_EINVAL otherwise);
+ * nodes below the cut (a larger subtree is a partition of its own), kept in pinned host memory as
+ * one word and one bit per node, which kernels read in place, once per iteration: the resident
+ * top-down pass, then the partitions' top-down and bottom-up passes (values, regrets and own
+ * reaches added into the resident per-pair accumulators), in runs of subtrees that a workgroup
+ * holds in LDS; the resident bottom-up; the infoset update. Where a level-cut subtree is too large
+ * for that, the levels down to subtrees that are not keep their values and reaches in a device
+ * window, which as many partitions share at a time as fit the largest one's size. The arithmetic
+ * is the node engine's (FP32, or FP64 with CFR_FLAG_FP64); device memory holds the resident levels,
+ * that window and the per-pair state. cut_level in 1 .. depth - 1, max_window_nodes >= 1 (CFR_EINVAL otherwise);
  * flags: CFR_FLAG_ALTERNATING, CFR_FLAG_FP64 (CFR_FLAG_NO_GRAPH and CFR_FLAG_NODE_ENGINE are
  * implied; others CFR_EINVAL).
  * cfr_plan_partitioned reports the sizes as cfr_plan does (workspace_bytes: this solver's device

@@ -31,7 +31,7 @@ struct cfr_solver {
                          // structure arrays, its real-valued pointers are null)
     bool fp64 = false;
     // subtree-partitioned, out-of-core solver (cfr_build_partitioned): the partitions' pinned
-    // host windows (one of the two, by precision)
+    // host records (one of the two, by precision)
     std::unique_ptr<cfr::PartDev<float>> part32;
     std::unique_ptr<cfr::PartDev<double>> part64;
     bool partitioned() const { return part32 != nullptr || part64 != nullptr; }
@@ -1052,8 +1052,8 @@ int check_partitioned_config(const cfr_config& c) {
     return CFR_OK;
 }
 
-// Device sizes of a partitioned solver: the resident levels and one window, every pair.
-Sizes partitioned_sizes(const cfr::Layout& L, const cfr::PartPlan& P, bool fp64) {
+// Device sizes of a partitioned solver: the resident levels and the window, every pair.
+Sizes partitioned_sizes(const cfr::Layout& L, const cfr::StreamPlan& P, bool fp64) {
     Sizes z;
     z.N = P.base + P.window;
     z.Hp = L.Hp; z.Qp = L.Qp; z.H0 = L.H0; z.Q0 = L.Q0; z.M = 0;
@@ -1085,7 +1085,9 @@ int cfr_plan_partitioned(const cfr_game* game, const cfr_config* config, int32_t
     cfr::PartPlan P;
     if ((rc = cfr::plan_partitions(L, cut_level, max_window_nodes, P, err)) != CFR_OK)
         return set_err(rc, err);
-    const Sizes z = partitioned_sizes(L, P, fp64);
+    cfr::StreamPlan stream_plan;
+    cfr::plan_stream(L, P, fp64, stream_plan, true);
+    const Sizes z = partitioned_sizes(L, stream_plan, fp64);
     cfr::Dev d{};
     cfr::Dev64 d64{};
     cfr::XDev x{};
@@ -1102,9 +1104,7 @@ int cfr_plan_partitioned(const cfr_game* game, const cfr_config* config, int32_t
     out->engine = ENGINE_NODE;
     out->workspace_bytes = static_cast<int64_t>(carve(d, d64, x, nullptr, z));
     if (n_partitions != nullptr) *n_partitions = P.parts;
-    if (host_bytes != nullptr)
-        *host_bytes = P.total * (4 * 3 + 1 + (fp64 ? 8 : 4)) + (P.total + P.parts) * 4 +
-                      static_cast<int64_t>(P.patch.size()) * 4;
+    if (host_bytes != nullptr) *host_bytes = stream_plan.host_bytes(fp64);
     return CFR_OK;
 }
 
@@ -1126,7 +1126,9 @@ int cfr_build_partitioned(const cfr_game* game, const cfr_config* config, int32_
     cfr::PartPlan P;
     if ((rc = cfr::plan_partitions(L, cut_level, max_window_nodes, P, err)) != CFR_OK)
         return set_err(rc, err);
-    const Sizes z = partitioned_sizes(L, P, fp64);
+    cfr::StreamPlan stream_plan;
+    cfr::plan_stream(L, P, fp64, stream_plan);
+    const Sizes z = partitioned_sizes(L, stream_plan, fp64);
     cfr::Dev d{};
     cfr::Dev64 d64{};
     cfr::XDev x{};
@@ -1143,7 +1145,7 @@ int cfr_build_partitioned(const cfr_game* game, const cfr_config* config, int32_
     s->canonical = false;  // the device holds the resident levels and a window, not the tree
     s->rule = rule_of(cfg);
     s->alternating = (cfg.flags & CFR_FLAG_ALTERNATING) != 0;
-    s->use_graph = false;  // each pass streams host memory through the window
+    s->use_graph = false;
     s->level_pure = L.level_pure;
     s->n_terminals = L.n_terminals;
     s->max_actions = L.max_actions;
@@ -1188,22 +1190,22 @@ int cfr_build_partitioned(const cfr_game* game, const cfr_config* config, int32_
             return rc;
         }
         s->part64 = std::make_unique<cfr::PartDev<double>>();
-        s->part64->plan = std::move(P);
+        s->part64->plan = std::move(stream_plan);
         s->part64->level_offset = L.level_offset;
-        rc = s->part64->upload(st);
+        rc = s->part64->upload();
     } else {
         if ((rc = upload(d.payoff, pay32, st)) || (rc = upload(d.prob, prob_tail, st))) {
             discard(s);
             return rc;
         }
         s->part32 = std::make_unique<cfr::PartDev<float>>();
-        s->part32->plan = std::move(P);
+        s->part32->plan = std::move(stream_plan);
         s->part32->level_offset = L.level_offset;
-        rc = s->part32->upload(st);
+        rc = s->part32->upload();
     }
     if (rc != 0) {
         discard(s);
-        return set_err(CFR_ENOMEM, "pinned host memory for the partition windows");
+        return set_err(CFR_ENOMEM, "pinned host memory for the partitions");
     }
     if (fp64) cfr::launch_reset(d64, st, true);
     else cfr::launch_reset(d, st, true);

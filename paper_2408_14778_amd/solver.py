@@ -408,7 +408,7 @@ class NPlayerSolver(Solver):
 class PartitionedSolver(Solver):
     """The subtree-partitioned, out-of-core iteration (cfr_build_partitioned): levels
     0 .. cut_level resident on the device, the subtrees below grouped into partitions of at most
-    max_window_nodes nodes held in pinned host memory and streamed through one device window per
+    max_window_nodes nodes held in pinned host memory, which kernels read in place once per
     iteration. Same update rules, schedules and precisions as Solver (node engine arithmetic);
     exploitability and node values are not available (the device never holds the whole tree):
     move the state into a Solver of the same game to evaluate it."""
