@@ -857,7 +857,8 @@ void launch_average(const DevT<F>& d, hipStream_t st) {
 }
 
 template <class F>
-void launch_best_response(const DevT<F>& d, const int32_t* lo, const int32_t* hlo, hipStream_t st) {
+void launch_best_response(const DevT<F>& d, const int32_t* lo, const int32_t* hlo, double* out,
+                          hipStream_t st) {
     if (d.D > 1 && br_path_applies(d.N, d.D)) {
         hipLaunchKernelGGL(k_br_reach_path<F>, dim3(blocks_for(lo[d.D])), dim3(kBlock), 0, st,
                            int64_t{lo[d.D]}, d.N, d.parent, d.node_player, d.node_edge, d.avgprob,
@@ -883,7 +884,7 @@ void launch_best_response(const DevT<F>& d, const int32_t* lo, const int32_t* hl
         if (b - a <= kWideNodes) value(k_br_value_wide<F>, blocks_for(int64_t{64} * (b - a)));
         else value(k_br_value_level<F>, blocks_for(b - a));
     }
-    hipLaunchKernelGGL(k_br_store<F>, dim3(1), dim3(64), 0, st, d.N, d.br_value, d.out2);
+    hipLaunchKernelGGL(k_br_store<F>, dim3(1), dim3(64), 0, st, d.N, d.br_value, out);
 }
 
 template <class F>
@@ -911,7 +912,7 @@ void launch_gather_q(const DevT<F>& d, const F* src, F* dst, hipStream_t st) {
     template void launch_value_range<F>(const DevT<F>&, int32_t, int32_t, hipStream_t);        \
     template void launch_infoset_pass<F>(const DevT<F>&, const UpdateRule&, hipStream_t);      \
     template void launch_best_response<F>(const DevT<F>&, const int32_t*, const int32_t*,      \
-                                          hipStream_t);                                        \
+                                          double*, hipStream_t);                               \
     template void launch_scatter_q<F>(const DevT<F>&, const F*, F*, hipStream_t);              \
     template void launch_gather_q<F>(const DevT<F>&, const F*, F*, hipStream_t);
 CFR_INSTANTIATE(float)

@@ -68,7 +68,6 @@ struct DevT {
     F* br_value;            // 2N: values under player 1's, player 2's best response
     int32_t* best;          // Hp
     F* stage;               // 2 * Qp (state and average-strategy transfers)
-    double* out2;           // 2 best-response values
     // pair numbering of the state arrays (canonical for the node engine, exec for the
     // block engine)
     int32_t* sq_offset;     // Hp + 1
@@ -151,10 +150,10 @@ void launch_infoset_pass(const DevT<F>& d, const UpdateRule& rule, hipStream_t s
 // Average strategy into d.avgprob (canonical order; chance tail copied at reset).
 template <class F>
 void launch_average(const DevT<F>& d, hipStream_t st);
-// Best responses of both players against d.avgprob; player i's value lands in d.out2[i - 1].
+// Best responses of both players against d.avgprob; player i's value lands in out[i - 1].
 template <class F>
 void launch_best_response(const DevT<F>& d, const int32_t* level_offset_host,
-                          const int32_t* infoset_level_offset_host, hipStream_t st);
+                          const int32_t* infoset_level_offset_host, double* out, hipStream_t st);
 // Whether a best response takes every level's reach in one launch of walks to the root (measured per
 // check: 2.6 million nodes of 15 levels 17 us against 49 us in 14 launches). The walks' work grows
 // with nodes times depth, the launches they replace with the depth alone.

@@ -121,6 +121,11 @@ int cfr_mlp_create(int32_t in_features, int32_t hidden, int32_t outputs, int32_t
     }
     n->st = static_cast<hipStream_t>(stream);
     n->step = 0;
+    if (hipHostMalloc(reinterpret_cast<void**>(&n->h_loss), sizeof(float), hipHostMallocDefault) !=
+        hipSuccess) {
+        delete n;
+        return cfr::set_error(CFR_ENOMEM, "pinned host memory for the loss");
+    }
     *out = n;
     return CFR_OK;
 }
@@ -195,7 +200,8 @@ int cfr_mlp_train_step(cfr_mlp* n, const void* x, const float* target, const flo
     ta.W3T = n->wbT + tr[2];
     ta.b1 = n->w + o[1]; ta.b2 = n->w + o[3]; ta.b3 = n->w + o[5];
     ta.A1 = n->A1; ta.A2 = n->A2; ta.dZ3 = n->dZ3; ta.dZ2 = n->dZ2; ta.dZ1 = n->dZ1;
-    ta.part = n->part; ta.loss = n->loss;
+    ta.part = n->part;
+    ta.loss = loss != nullptr ? n->h_loss : n->loss;
     ta.w = n->w; ta.g = n->g; ta.m = n->m; ta.v = n->v;
     ta.wb = n->wb; ta.wbT = n->wbT; ta.wbP = n->wbP;
     ta.lr = lr; ta.beta1 = b1; ta.beta2 = b2; ta.eps = eps; ta.c1 = c1; ta.c2 = c2;
@@ -221,17 +227,21 @@ int cfr_mlp_train_step(cfr_mlp* n, const void* x, const float* target, const flo
         cfr::launch_colsum(B, H, n->dZ1, n->g + o[1], n->st, n->part);
         cfr::launch_adam(n->n_params, n->w, n->g, n->m, n->v, n->wb, lr, b1, b2, eps, c1, c2, n->st);
         transpose_weights(n);
+        if (loss != nullptr)
+            MLP_TRY(hipMemcpyAsync(n->h_loss, n->loss, 4, hipMemcpyDeviceToHost, n->st), "loss copy");
     }
     MLP_TRY(hipGetLastError(), "train launch");
     if (loss != nullptr) {
-        MLP_TRY(hipMemcpyAsync(loss, n->loss, 4, hipMemcpyDeviceToHost, n->st), "loss copy");
         MLP_TRY(hipStreamSynchronize(n->st), "train synchronise");
+        *loss = *n->h_loss;
     }
     return CFR_OK;
 }
 
 int cfr_mlp_destroy(cfr_mlp* n) {
-    if (n != nullptr) (void)hipStreamSynchronize(n->st);
+    if (n == nullptr) return CFR_OK;
+    (void)hipStreamSynchronize(n->st);
+    (void)hipHostFree(n->h_loss);
     delete n;
     return CFR_OK;
 }

@@ -24,6 +24,7 @@ struct cfr_mlp {
     float *Z3, *loss;
     float* part;  // partials of the weight and bias gradients
     int64_t step;
+    float* h_loss;  // pinned: a step's loss for the caller, written by the kernel in place
 };
 
 namespace cfr {

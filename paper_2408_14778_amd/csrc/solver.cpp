@@ -38,7 +38,9 @@ struct cfr_solver {
     ~cfr_solver() {
         if (part32) part32->release();
         if (part64) part64->release();
+        if (br_out != nullptr) (void)hipHostFree(br_out);
     }
+    double* br_out = nullptr;  // pinned: the best-response values, written by the kernels in place
     // small game: whole iterations in one launch (the one of the solver's precision is set up)
     cfr::Resident<float> res32;
     cfr::Resident<double> res64;
@@ -250,7 +252,6 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         // the node engine in double precision: structure shared with d, values here
         d.T = c.take<int64_t>(1);
         d.best = c.take<int32_t>(Hp);
-        d.out2 = c.take<double>(2 * static_cast<int64_t>(z.n_games));
         d.sq_offset = d.q_offset;
         d.sq_input = d.q_input;
         d64.N = N; d64.Hp = Hp; d64.Qp = Qp; d64.H0 = H0; d64.Q0 = Q0; d64.M = M; d64.D = D;
@@ -261,7 +262,7 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         d64.chance_id = d.chance_id; d64.cq_offset = d.cq_offset;
         d64.member_offset = d.member_offset; d64.members = d.members; d64.q_input = d.q_input;
         d64.node_slot = d.node_slot; d64.slot_base = d.slot_base;
-        d64.T = d.T; d64.best = d.best; d64.out2 = d.out2;
+        d64.T = d.T; d64.best = d.best;
         d64.sq_offset = d.sq_offset; d64.sq_input = d.sq_input;
         d64.players = z.players;
         d64.payoff = c.take<double>(cols * N);
@@ -299,7 +300,6 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         d.best = c.take<int32_t>(Hp);
     }
     d.stage = c.take<float>(2 * Qp);
-    d.out2 = c.take<double>(2 * static_cast<int64_t>(z.n_games));
     d.sq_offset = d.q_offset;
     d.sq_input = d.q_input;
     x = cfr::XDev{};
@@ -346,7 +346,6 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         x.T = d.T;
         x.br_reach = c.take<float>(2 * N);
         x.br_value = c.take<float>(2 * N);
-        x.out2 = d.out2;
         d.sq_offset = x.q_offset;
         d.sq_input = x.q_input;
     }
@@ -417,6 +416,16 @@ void discard(cfr_solver* s) {
     if (s->exec != nullptr) (void)hipGraphExecDestroy(s->exec);
     if (s->graph != nullptr) (void)hipGraphDestroy(s->graph);
     delete s;
+}
+
+// Pinned memory for a solver's best-response values (a copy to the caller's own memory would go through
+// a staging launch and a second wait: 11 us of a check).
+int best_response_out(cfr_solver* s) {
+    if (hipHostMalloc(reinterpret_cast<void**>(&s->br_out), 2 * sizeof(double) * s->n_games,
+                      hipHostMallocDefault) == hipSuccess)
+        return CFR_OK;
+    s->br_out = nullptr;
+    return set_err(CFR_ENOMEM, "pinned host memory for the best-response values");
 }
 
 // Validates a configuration (null: the defaults); CFR_OK or an error code with a message.
@@ -997,6 +1006,10 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
         discard(s);
         return hip_err(e, "build synchronise");
     }
+    if (s->players == 0 && (rc = best_response_out(s)) != CFR_OK) {
+        discard(s);
+        return rc;
+    }
     // (a resident game's iterations need no graph)
     if (s->use_graph && !s->resident && (rc = capture(s)) != CFR_OK) {
         discard(s);
@@ -1516,21 +1529,20 @@ int cfr_exploitability(cfr_solver* s, double* expl, double br_value[2]) {
     if (s->fp64) {
         cfr::launch_average(s->dev64, s->stream);
         cfr::launch_best_response(s->dev64, s->level_offset.data(), s->infoset_level_offset.data(),
-                                  s->stream);
+                                  s->br_out, s->stream);
     } else {
         cfr::launch_average(s->dev, s->stream);
         if (s->engine == ENGINE_BLOCK) {
-            cfr::launch_x_best_response(s->xdev, s->dev.avgprob, s->stream);
+            cfr::launch_x_best_response(s->xdev, s->dev.avgprob, s->br_out, s->stream);
         } else {
             cfr::launch_best_response(s->dev, s->level_offset.data(),
-                                      s->infoset_level_offset.data(), s->stream);
+                                      s->infoset_level_offset.data(), s->br_out, s->stream);
         }
     }
-    int rc = check_hip("best response launch");
+    const int rc = check_hip("best response launch");
     if (rc != CFR_OK) return rc;
-    double br[2];
-    HIP_TRY(hipMemcpyAsync(br, s->dev.out2, sizeof br, hipMemcpyDeviceToHost, s->stream), "br copy");
     HIP_TRY(hipStreamSynchronize(s->stream), "exploitability synchronise");
+    const double* br = s->br_out;
     *expl = 0.5 * (br[0] + br[1]);
     if (br_value != nullptr) {
         br_value[0] = br[0];
@@ -1923,6 +1935,10 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
         discard(s);
         return hip_err(e, "build synchronise");
     }
+    if ((rc = best_response_out(s)) != CFR_OK) {
+        discard(s);
+        return rc;
+    }
     if (s->use_graph && (rc = capture(s)) != CFR_OK) {
         discard(s);
         return rc;
@@ -1936,13 +1952,10 @@ int cfr_exploitability_batch(cfr_solver* s, double* expl, double* br_values, int
     if (n_games != s->n_games) return set_err(CFR_EINVAL, "n_games does not match the batch");
     if (s->engine != ENGINE_BLOCK) return set_err(CFR_EINVAL, "not a batch solver");
     cfr::launch_average(s->dev, s->stream);
-    cfr::launch_x_best_response(s->xdev, s->dev.avgprob, s->stream);
-    int rc = check_hip("best response launch");
-    if (rc != CFR_OK) return rc;
-    std::vector<double> br(2 * static_cast<size_t>(n_games));
-    HIP_TRY(hipMemcpyAsync(br.data(), s->dev.out2, br.size() * sizeof(double), hipMemcpyDeviceToHost,
-                           s->stream), "br copy");
+    cfr::launch_x_best_response(s->xdev, s->dev.avgprob, s->br_out, s->stream);
+    if (const int rc = check_hip("best response launch"); rc != CFR_OK) return rc;
     HIP_TRY(hipStreamSynchronize(s->stream), "exploitability synchronise");
+    const double* br = s->br_out;
     for (int32_t g = 0; g < n_games; ++g) {
         expl[g] = 0.5 * (br[2 * g] + br[2 * g + 1]);
         if (br_values != nullptr) {

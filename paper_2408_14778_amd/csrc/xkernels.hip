@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(1024) k_x_reach_pairs(int32_t t0, int64_t N,
 // (tiles as in k_x_reach, one node per lane) walks up through its ancestors to the first stored
 // level (nodes below `stop`), at most kPathDepth steps, collecting the edge probabilities and
 // actors, then multiplies them onto the ancestor's reach from the top down, in the order the
-// level-by-level pass uses.
+// level-by-level pass uses. With a T it also counts the iteration (launch_x_iteration).
 __global__ void __launch_bounds__(256) k_x_reach_path(int32_t t0, int32_t stop, int64_t N,
                                                       const int32_t* __restrict__ tile_lo,
                                                       const int32_t* __restrict__ tile_hi,
@@ -238,7 +238,8 @@ __global__ void __launch_bounds__(256) k_x_reach_path(int32_t t0, int32_t stop, 
                                                       const int32_t* __restrict__ edge,
                                                       const int8_t* __restrict__ meta,
                                                       const float* __restrict__ prob,
-                                                      float* __restrict__ reach) {
+                                                      float* __restrict__ reach, int64_t* T) {
+    if (T != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *T += 1;
     const int32_t t = t0 + static_cast<int32_t>(xcd_tile());
     const int32_t x = tile_lo[t] + static_cast<int32_t>(threadIdx.x);
     if (x >= tile_hi[t] || (meta[x] & 3) == 0) return;
@@ -332,6 +333,7 @@ struct UpArgs {
     float* R;
     float* S;
     int64_t* T;
+    int32_t t_add;  // the iteration is *T + t_add (0: it has been counted already)
     UpdateRule rule;
     // derive_reach != 0 (the deepest decision level, whose children are all terminal): the
     // level had no top-down launch; a member's player planes are its parent's times its edge
@@ -572,7 +574,7 @@ __device__ __forceinline__ void up_chunk(const UpArgs& a, int32_t c, float (*s_c
             if (!kPrefetch) load_pairs<KMAX>(a, o, k, pr, ps, pp);
             update_infoset<KMAX>(a, a.R + o, a.S + o, a.prob + o, k, player, 0,
                                  nm < CH ? nm : CH, pr, ps, pp, s_con, s_own,
-                                 static_cast<float>(*a.T + 1));
+                                 static_cast<float>(*a.T + a.t_add));
         }
         return;
     }
@@ -592,7 +594,7 @@ __device__ __forceinline__ void up_chunk(const UpArgs& a, int32_t c, float (*s_c
         }
         if (u > 0 || !kPrefetch) load_pairs<KMAX>(a, o, k, pr, ps, pp);
         update_infoset<KMAX>(a, a.R + o, a.S + o, a.prob + o, k, player, slo, shi, pr, ps, pp,
-                             s_con, s_own, static_cast<float>(*a.T + 1));
+                             s_con, s_own, static_cast<float>(*a.T + a.t_add));
     }
 }
 
@@ -680,7 +682,7 @@ __global__ void __launch_bounds__(T) k_x_pack(UpArgs a, PackArgs pa) {
     {
         const int32_t* d = reinterpret_cast<const int32_t*>(pa.packs + pa.first + xcd_tile());
         for (int w = tid; w < kDescWords; w += T) s_desc[w] = d[w];
-        if (tid == 0) s_t = static_cast<float>(*a.T + 1);  // read before this workgroup counts
+        if (tid == 0) s_t = static_cast<float>(*a.T + a.t_add);  // read before this workgroup counts
     }
     __syncthreads();
     const PackDesc& pk = *reinterpret_cast<const PackDesc*>(s_desc);
@@ -1292,6 +1294,7 @@ UpArgs up_args(const XDev& x, const UpdateRule& rule) {
     a.R = x.R;
     a.S = x.S;
     a.T = x.T;
+    a.t_add = 1;
     a.rule = rule;
     a.derive_reach = 0;
     a.kp_packed = x.kp_packed;
@@ -1492,6 +1495,12 @@ void launch_x_iteration(const XDev& x, const UpdateRule& rule, hipStream_t st, L
         }
     }
     const int32_t fp = x.path_reach;
+    // Counting the iteration. k_x_up_top or the last pack launch does it where there is one (every
+    // read of T comes before). A forest has neither: its path launch counts ahead of the
+    // iteration, which then reads T itself (a launch for the count alone takes 3.4 us of an
+    // iteration; 48 subgames 203 us).
+    bool counted = false;
+    const bool early = rule.count && x.fused_up <= 0 && x.n_tiers == 0;
     if (fp > fr) {
         const int32_t t0 = x.t_level_offset_host[1 + fr], nt = x.t_level_offset_host[fp + 1] - t0;
         if (nt > 0) {
@@ -1499,7 +1508,9 @@ void launch_x_iteration(const XDev& x, const UpdateRule& rule, hipStream_t st, L
             for (int32_t l = 1 + fr; l <= fp; ++l) units += x.reach_units_host[l];
             pre(XK_REACH, -2, units);
             hipLaunchKernelGGL(k_x_reach_path, dim3(nt), dim3(kPathThreads), 0, st, t0, lo[1 + fr],
-                               x.N, x.tile_lo, x.tile_hi, x.parent, x.edge, x.meta, x.prob, x.reach);
+                               x.N, x.tile_lo, x.tile_hi, x.parent, x.edge, x.meta, x.prob, x.reach,
+                               early ? x.T : nullptr);
+            counted = early;
             post(XK_REACH);
         }
     }
@@ -1512,7 +1523,8 @@ void launch_x_iteration(const XDev& x, const UpdateRule& rule, hipStream_t st, L
         launch_reach_level(x, l, st);
         post(XK_REACH);
     }
-    const UpArgs a = up_args(x, rule);
+    UpArgs a = up_args(x, rule);
+    if (counted) a.t_add = 0;
     // the subtree packs, tier by tier: top-down from the highest tier, tier 1 through both
     // sweeps, bottom-up from tier 2 (one workgroup per pack)
     // with no upper level to finish bottom-up, the last pack launch counts the iteration
@@ -1556,7 +1568,7 @@ void launch_x_iteration(const XDev& x, const UpdateRule& rule, hipStream_t st, L
         pre(XK_UP, -1, x.m_level_offset_host[fu] - x.m_level_offset_host[0]);
         hipLaunchKernelGGL(k_x_up_top, dim3(1), dim3(kFuseThreads), 0, st, a, t, up_warm(x, fu));
         post(XK_UP);
-    } else if (rule.count && !pack_counts) {
+    } else if (rule.count && !pack_counts && !counted) {
         // the linear-averaging weight of every launch above read T: count the iteration last
         hipLaunchKernelGGL(k_x_tick, dim3(1), dim3(64), 0, st, x.T);
     }
@@ -1589,7 +1601,7 @@ void launch_br_cap(const XDev& x, const BrArgs& a, int32_t l, hipStream_t st) {
 
 }  // namespace
 
-void launch_x_best_response(const XDev& x, const float* avgprob, hipStream_t st) {
+void launch_x_best_response(const XDev& x, const float* avgprob, double* out, hipStream_t st) {
     const int32_t* lo = x.level_offset_host;
     if (x.D > 1 && br_path_applies(x.N, x.D))
         hipLaunchKernelGGL(k_x_br_reach_path, dim3(blocks_of(lo[x.D] - lo[1], kBlock)), dim3(kBlock), 0,
@@ -1622,7 +1634,7 @@ void launch_x_best_response(const XDev& x, const float* avgprob, hipStream_t st)
     }
     const int32_t n_roots = lo[1];
     hipLaunchKernelGGL(k_x_store_roots, dim3(blocks_for(n_roots)), dim3(kBlock), 0, st, n_roots, x.N,
-                       x.br_value, x.out2);
+                       x.br_value, out);
 }
 
 void launch_x_values_to_canonical(const XDev& x, float* dst, hipStream_t st) {

@@ -137,7 +137,6 @@ struct XDev {
     int64_t* T;
     float* br_reach;  // 2N: pi_{-1}, pi_{-2}
     float* br_value;  // 2N: values under player 1's, player 2's best response
-    double* out2;
 };
 
 // How many first levels the single-workgroup kernels take (from the plan's level tables).
@@ -157,8 +156,8 @@ void launch_x_reset(const XDev& x, hipStream_t st);
 void launch_x_iteration(const XDev& x, const UpdateRule& rule, hipStream_t st,
                         LaunchTimer* timer = nullptr);
 // Best responses of both players to sigma-bar (avgprob: exec pairs, then sigma_0); the root
-// values land in out2[2 g], out2[2 g + 1].
-void launch_x_best_response(const XDev& x, const float* avgprob, hipStream_t st);
+// values land in out[2 g], out[2 g + 1].
+void launch_x_best_response(const XDev& x, const float* avgprob, double* out, hipStream_t st);
 void launch_x_values_to_canonical(const XDev& x, float* dst, hipStream_t st);
 void launch_x_reach_to_canonical(const XDev& x, float* dst, hipStream_t st);
 
