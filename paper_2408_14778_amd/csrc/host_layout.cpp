@@ -17,8 +17,9 @@ namespace cfr {
 
 // Flattens and plans every game on host threads; all must be level pure with <= 16 actions.
 int plan_games(const cfr_game* games, int32_t n, std::vector<cfr::ExecPlan>& plans,
-               int32_t& max_actions, std::string& err, bool packs) {
+               int32_t& max_actions, std::string& err, bool packs, std::vector<Layout>* layouts) {
     plans.assign(n, cfr::ExecPlan());
+    if (layouts != nullptr) layouts->assign(n, Layout());
     std::vector<int> codes(n, CFR_OK);
     std::vector<std::string> errs(n);
     std::vector<int32_t> maxa(n, 0);
@@ -40,6 +41,7 @@ int plan_games(const cfr_game* games, int32_t n, std::vector<cfr::ExecPlan>& pla
             if (rc == CFR_OK) rc = cfr::build_exec_plan(L, plans[g], errs[g], deep);
             maxa[g] = L.max_actions;
             codes[g] = rc;
+            if (layouts != nullptr) (*layouts)[g] = std::move(L);
         }
     };
     // subtree packs are instantiated for at most 4 actions per infoset, over the whole batch:

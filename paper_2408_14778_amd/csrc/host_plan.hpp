@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "../../include/cfr.h"
+#include "flatten.hpp"
 #include "xplan.hpp"
 
 namespace cfr {
@@ -16,8 +17,9 @@ int set_error(int code, const std::string& msg);
 
 // Flattens and plans every game on host threads (CFR_ELEVEL or CFR_EINVAL unless every game
 // has level-pure infosets and at most 16 actions). packs: plan subtree packs where the batch
-// allows them (at most 4 actions in every game).
+// allows them (at most 4 actions in every game). layouts: the games' layouts are kept there too.
 int plan_games(const cfr_game* games, int32_t n, std::vector<ExecPlan>& plans,
-               int32_t& max_actions, std::string& err, bool packs);
+               int32_t& max_actions, std::string& err, bool packs,
+               std::vector<Layout>* layouts = nullptr);
 
 }  // namespace cfr

@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <functional>
 #include <thread>
 
 namespace cfr {
@@ -13,6 +14,28 @@ namespace {
 // all latency, and more workgroups only make the barrier dearer.
 constexpr int64_t kBinNodes = 3000;
 
+// Runs the jobs, each on a thread of its own where n (the nodes they go over) is large. False: one
+// threw.
+bool run_all(int64_t n, const std::vector<std::function<void()>>& jobs) {
+    std::atomic<bool> failed{false};
+    auto guarded = [&](const std::function<void()>& job) {
+        try {
+            job();
+        } catch (...) {
+            failed = true;
+        }
+    };
+    std::vector<std::thread> pool;
+    size_t i = 0;
+    if (n >= 200000) try {
+            for (; i + 1 < jobs.size(); ++i) pool.emplace_back([&, i] { guarded(jobs[i]); });
+        } catch (...) {  // fewer threads
+        }
+    for (; i < jobs.size(); ++i) guarded(jobs[i]);
+    for (std::thread& th : pool) th.join();
+    return !failed;
+}
+
 int64_t columns(const ResSizes& z) { return z.players > 0 ? z.players : 1; }
 int64_t planes(const ResSizes& z) { return z.players > 0 ? z.players : 2; }
 
@@ -20,7 +43,7 @@ int64_t planes(const ResSizes& z) { return z.players > 0 ? z.players : 2; }
 
 int32_t resident_max_bins(const ResSizes& z) {
     const bool block = z.players == 0 && z.real_bytes == 4 && z.level_pure;
-    return 1 + (block ? kResRoundsBlock : kResRounds) * (kResTeam - 1);
+    return 1 + (z.forest ? kResRoundsForest : block ? kResRoundsBlock : kResRounds) * (kResTeam - 1);
 }
 
 bool resident_fits(const ResSizes& z) {
@@ -28,12 +51,98 @@ bool resident_fits(const ResSizes& z) {
            z.max_actions <= kResMaxActions && z.pairs + z.chance_pairs < (int64_t{1} << 28) &&
            z.players < 15 &&
            z.real_bytes * (columns(z) * z.nodes + planes(z) * z.decision) <=
-               kResLds * resident_max_bins(z);
+               kResLds * resident_max_bins(z) &&
+           // (one round of bins that leaves them no room to be uneven is not worth its search)
+           (!z.forest || (z.real_bytes * (2 * z.nodes + 2 * z.decision) + 8 * z.decision) * 4 <=
+                             3 * kResLds * resident_max_bins(z));
 }
 
 int64_t resident_max_table(const ResSizes& z) { return int64_t{resident_max_bins(z)} * (z.depth + 3); }
 int64_t resident_max_roots(const ResSizes& z) { return std::min<int64_t>(kResTrunk, z.decision); }
 int64_t resident_max_path(const ResSizes& z) { return kResPath * resident_max_roots(z); }
+
+Layout forest_layout(const std::vector<Layout>& games) {
+    const size_t n = games.size();
+    Layout L;
+    L.N = 1;
+    std::vector<int64_t> h_base(n), q_base(n), q0_base(n), m_base(n);
+    for (size_t g = 0; g < n; ++g) {
+        h_base[g] = L.Hp; q_base[g] = L.Qp; q0_base[g] = L.Q0; m_base[g] = L.n_members;
+        L.N += games[g].N; L.Hp += games[g].Hp; L.Qp += games[g].Qp; L.Q0 += games[g].Q0;
+        L.n_members += games[g].n_members;
+        L.D = std::max(L.D, games[g].D + 1);
+    }
+    // level l + 1: level l of every game, game after game
+    std::vector<std::vector<int64_t>> base(n, std::vector<int64_t>(L.D + 1, 0));
+    L.level_offset = {0};
+    int64_t at = 1;
+    for (int32_t l = 0; l <= L.D; ++l) {
+        L.level_offset.push_back(static_cast<int32_t>(at));
+        for (size_t g = 0; g < n; ++g) {
+            base[g][l] = at;
+            if (l <= games[g].D) at += games[g].level_offset[l + 1] - games[g].level_offset[l];
+        }
+    }
+    L.parent.resize(L.N);
+    L.child_begin.resize(L.N + 1);
+    L.node_player.resize(L.N);
+    L.node_infoset.resize(L.N);
+    L.node_edge.resize(L.N);
+    L.payoff.resize(L.N);
+    L.q_offset.resize(L.Hp + 1);
+    L.member_offset.resize(L.Hp + 1);
+    L.infoset_player.resize(L.Hp);
+    L.members.resize(L.n_members);
+    L.parent[0] = L.node_infoset[0] = L.node_edge[0] = -1;
+    L.node_player[0] = 0;
+    L.payoff[0] = 0.0f;
+    L.child_begin[0] = 1;
+    L.child_begin[L.N] = static_cast<int32_t>(L.N);
+    L.q_offset[L.Hp] = static_cast<int32_t>(L.Qp);
+    L.member_offset[L.Hp] = static_cast<int32_t>(L.n_members);
+    for (const Layout& G : games)
+        L.chance_prob.insert(L.chance_prob.end(), G.chance_prob.begin(), G.chance_prob.end());
+    const int32_t Qp = static_cast<int32_t>(L.Qp), Q0 = static_cast<int32_t>(L.Q0);
+    for (size_t g = 0; g < n; ++g) {
+        const Layout& G = games[g];
+        for (int32_t l = 0; l <= G.D; ++l) {
+            const int32_t lo = G.level_offset[l];
+            const int32_t down = static_cast<int32_t>(base[g][l + 1]) - G.level_offset[l + 1];
+            const int32_t up = l > 0 ? static_cast<int32_t>(base[g][l - 1]) - G.level_offset[l - 1] : 0;
+            const int32_t here = static_cast<int32_t>(base[g][l]) - lo;
+            for_ranges(G.level_offset[l + 1] - lo, [&, l, lo, down, up, here](int64_t i0, int64_t i1) {
+                for (int64_t v = lo + i0; v < lo + i1; ++v) {
+                    const int64_t i = v + here;
+                    const int32_t e = G.node_edge[v];
+                    L.parent[i] = l > 0 ? G.parent[v] + up : 0;
+                    L.child_begin[i] = G.child_begin[v] + down;
+                    L.node_player[i] = G.node_player[v];
+                    L.node_infoset[i] = G.node_player[v] > 0
+                                            ? G.node_infoset[v] + static_cast<int32_t>(h_base[g]) : -1;
+                    L.node_edge[i] = l == 0 ? Qp + Q0 + static_cast<int32_t>(g)
+                                     : e < G.Qp ? e + static_cast<int32_t>(q_base[g])
+                                                : Qp + static_cast<int32_t>(q0_base[g] + (e - G.Qp));
+                    L.payoff[i] = G.payoff[v];
+                }
+            });
+        }
+        for (int64_t h = 0; h < G.Hp; ++h) {
+            const int64_t i = h_base[g] + h;
+            L.q_offset[i] = G.q_offset[h] + static_cast<int32_t>(q_base[g]);
+            L.member_offset[i] = G.member_offset[h] + static_cast<int32_t>(m_base[g]);
+            L.infoset_player[i] = G.infoset_player[h];
+            int32_t l = 0;
+            for (int32_t m = G.member_offset[h]; m < G.member_offset[h + 1]; ++m) {
+                const int32_t v = G.members[m];
+                while (v >= G.level_offset[l + 1]) ++l;
+                L.members[m_base[g] + m] = v - G.level_offset[l] + static_cast<int32_t>(base[g][l]);
+            }
+        }
+    }
+    L.Q0 += static_cast<int64_t>(n);
+    L.chance_prob.resize(L.Q0, 1.0f);
+    return L;
+}
 
 bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResSizes& z,
                     ResPlan& P) {
@@ -169,11 +278,6 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
     const bool team = P.mode == RES_TEAM;
     const int32_t W = D + 3;
     P.table.assign(static_cast<size_t>(P.bins) * W, Rec4{0, 0, 0, 0});
-    P.rec.resize(nd);
-    P.slot.assign(nd, 0);
-    P.reach_c.resize(nd);
-    P.rank_node.resize(nd);
-    P.node.resize(N + P.roots);
     P.root_rank.resize(P.roots);
     P.ext.resize(P.roots);
     P.path.assign(static_cast<size_t>(P.roots) * P.path_len, 0);
@@ -189,49 +293,64 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
         while (g < 6 && (1 << g) < kmax) ++g;
         glog[l] = kmax > 256 ? kResWide : g;
     }
+    std::vector<double> rc;
+    std::vector<int32_t> slot, lnode, lrank;
     // chance products (rounded to float after every factor in single precision, as the level by
     // level launches form them)
-    const bool f64 = real == 8;
-    std::vector<double> rc(N, 1.0);
-    for (int64_t v = 1; v < N; ++v) {
-        if (L.node_player[v] < 0) continue;  // (terminal nodes need none)
-        const int32_t p = L.parent[v];
-        double x = rc[p];
-        if (L.node_player[p] == 0) {
-            const int64_t i = L.node_edge[v] - L.Qp;
-            x = f64 ? x * L.chance_prob64[i]
-                    : static_cast<double>(static_cast<float>(x) * L.chance_prob[i]);
+    const auto chance_products = [&] {
+        const bool f64 = real == 8;
+        rc.assign(N, 1.0);
+        for (int64_t v = 1; v < N; ++v) {
+            if (L.node_player[v] < 0) continue;  // (terminal nodes need none)
+            const int32_t p = L.parent[v];
+            double x = rc[p];
+            if (L.node_player[p] == 0) {
+                const int64_t i = L.node_edge[v] - L.Qp;
+                x = f64 ? x * L.chance_prob64[i]
+                        : static_cast<double>(static_cast<float>(x) * L.chance_prob[i]);
+            }
+            rc[v] = x;
         }
-        rc[v] = x;
-    }
+    };
     // infosets: the trunk's first, then by pair (through the pairs: no sort); their contribution
     // slots in that order
-    std::vector<int8_t> of_trunk(L.Hp, 0);
-    if (team)
-        for (int32_t v : in_trunk)
-            if (L.node_player[v] > 0) of_trunk[L.node_infoset[v]] = 1;
-    std::vector<int32_t> order, at_pair(L.Qp, -1);
-    order.reserve(L.Hp);
-    for (int64_t h = 0; h < L.Hp; ++h) at_pair[q_of[h]] = static_cast<int32_t>(h);
-    for (int pass = 1; pass >= 0; --pass)
-        for (int64_t q = 0; q < L.Qp; ++q)
-            if (at_pair[q] >= 0 && of_trunk[at_pair[q]] == pass) order.push_back(at_pair[q]);
-    P.sets.resize(L.Hp);
-    std::vector<int32_t> slot(N, 0);
-    int64_t at = 0;
-    for (int64_t i = 0; i < L.Hp; ++i) {
-        const int32_t h = order[i];
-        const int32_t m0 = L.member_offset[h], n = L.member_offset[h + 1] - m0;
-        const int32_t k = L.q_offset[h + 1] - L.q_offset[h];
-        P.trunk_sets += of_trunk[h];
-        P.max_actions = std::max(P.max_actions, k);
-        P.sets[i] = Rec4{q_of[h], static_cast<int32_t>(at), n, k | (L.infoset_player[h] << 24)};
-        for (int32_t j = 0; j < n; ++j)
-            slot[L.members[m0 + j]] =
-                static_cast<int32_t>(at + static_cast<int64_t>(j) * res_stride(k, z.real_bytes));
-        at += static_cast<int64_t>(n) * res_stride(k, z.real_bytes);
-    }
-    P.mean_members = L.Hp > 0 ? static_cast<int32_t>(L.n_members / L.Hp) : 0;
+    const auto number_sets = [&] {
+        std::vector<int8_t> of_trunk(L.Hp, 0);
+        if (team)
+            for (int32_t v : in_trunk)
+                if (L.node_player[v] > 0) of_trunk[L.node_infoset[v]] = 1;
+        std::vector<int32_t> order, at_pair(L.Qp, -1);
+        order.reserve(L.Hp);
+        for (int64_t h = 0; h < L.Hp; ++h) at_pair[q_of[h]] = static_cast<int32_t>(h);
+        for (int pass = 1; pass >= 0; --pass)
+            for (int64_t q = 0; q < L.Qp; ++q)
+                if (at_pair[q] >= 0 && of_trunk[at_pair[q]] == pass) order.push_back(at_pair[q]);
+        P.sets.resize(L.Hp);
+        slot.assign(N, 0);
+        int64_t at = 0;
+        for (int64_t i = 0; i < L.Hp; ++i) {
+            const int32_t h = order[i];
+            const int32_t m0 = L.member_offset[h], n = L.member_offset[h + 1] - m0;
+            const int32_t k = L.q_offset[h + 1] - L.q_offset[h];
+            P.trunk_sets += of_trunk[h];
+            P.max_actions = std::max(P.max_actions, k);
+            P.sets[i] = Rec4{q_of[h], static_cast<int32_t>(at), n, k | (L.infoset_player[h] << 24)};
+            for (int32_t j = 0; j < n; ++j)
+                slot[L.members[m0 + j]] =
+                    static_cast<int32_t>(at + static_cast<int64_t>(j) * res_stride(k, z.real_bytes));
+            at += static_cast<int64_t>(n) * res_stride(k, z.real_bytes);
+        }
+        P.mean_members = L.Hp > 0 ? static_cast<int32_t>(L.n_members / L.Hp) : 0;
+    };
+    if (!run_all(N, {[&] { P.rec.resize(nd); }, [&] { P.slot.assign(nd, 0); },
+                     [&] { P.reach_c.resize(nd); },
+                     [&] {
+                         P.rank_node.resize(nd);
+                         P.node.resize(N + P.roots);
+                     },
+                     [&] { lnode.assign(N, -1); }, [&] { lrank.assign(N, -1); }, chance_products,
+                     number_sets}))
+        return false;
     // where each bin's ranks and nodes begin
     std::vector<int64_t> rbase_of(P.bins, 0), nbase_of(P.bins, 0);
     if (team) {
@@ -248,7 +367,6 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
     }
     // the bins: local numbers level by level, records (the trunk first: its leaves are numbered
     // again in their own bins; the others on several threads)
-    std::vector<int32_t> lnode(N, -1), lrank(N, -1);
     std::vector<int32_t> bin_nodes(P.bins, 0), bin_ranks(P.bins, 0);
     auto fill_bin = [&](int32_t b) {
         std::vector<int32_t> now, next;

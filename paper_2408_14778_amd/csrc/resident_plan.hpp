@@ -3,8 +3,10 @@
 // records that one launch iterates from start to end.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "flatten.hpp"
@@ -25,7 +27,10 @@ constexpr int32_t kResTeam = 256;       // workgroups of a team: one per CU
 // (5.5 million nodes: 124 against 140 us per iteration; 3.3 million, two bins: 84 against 125 us),
 // the trend crosses near 7 million; the node engine's alternatives are two to four times slower
 // (2.2 million nodes in double precision, two bins: 78 against 229 us).
-constexpr int32_t kResRoundsBlock = 3, kResRounds = 8;
+// A batch keeps to one: its records cost more to lay out than its iterations gain beyond (10 games of
+// 2.8 million nodes in all, two bins: 103 -> 79 us per iteration for 66 ms; 12 of 1.6 million, one
+// bin: 84 -> 44 us).
+constexpr int32_t kResRoundsBlock = 3, kResRounds = 8, kResRoundsForest = 1;
 constexpr int32_t kResMaxBins = 1 + kResRounds * (kResTeam - 1);
 constexpr int32_t kResTrunk = 32768;    // subtrees
 constexpr int32_t kResPath = 24;        // levels above them
@@ -42,8 +47,24 @@ constexpr int32_t res_stride(int32_t k, int32_t real_bytes) {
 struct ResSizes {
     int64_t nodes = 0, decision = 0, members = 0, infosets = 0, pairs = 0, chance_pairs = 0;
     int32_t depth = 0, max_actions = 0, players = 0, real_bytes = 4;
-    bool level_pure = true;
+    bool level_pure = true, forest = false;
 };
+// f(begin, end) over parts of 0 .. n - 1, on several threads where n is large. f does not throw.
+template <class Fn>
+void for_ranges(int64_t n, const Fn& f) {
+    const int64_t parts =
+        n < 200000 ? 1 : std::max(1u, std::min(8u, std::thread::hardware_concurrency()));
+    std::vector<std::thread> pool;
+    int64_t i = 0;
+    try {
+        for (; i + 1 < parts; ++i)
+            pool.emplace_back([&f, n, parts, i] { f(n * i / parts, n * (i + 1) / parts); });
+    } catch (...) {  // fewer threads
+    }
+    f(n * i / parts, n);
+    for (std::thread& th : pool) th.join();
+}
+
 // Whether a game of these sizes may run resident (the plan then decides); the plan's arrays are
 // bounded by these sizes alone.
 bool resident_fits(const ResSizes& z);
@@ -86,6 +107,11 @@ struct ResPlan {
     int64_t contributions = 0;
     int32_t max_actions = 1, mean_members = 0;
 };
+
+// A batch as one game: a chance node above the games' roots deals each of them with probability 1, on
+// edges past the games' own (its value is a sum that nobody reads). Infosets, pairs and chance pairs
+// game after game in their canonical orders.
+Layout forest_layout(const std::vector<Layout>& games);
 
 // Plans layout L; q_of[h]: the first pair of canonical rational infoset h in the engine's order.
 // False: no split whose bins fit (the game stays on the level-by-level launches).

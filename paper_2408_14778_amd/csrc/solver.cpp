@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <future>
 #include <memory>
 #include <cmath>
 #include <cstring>
@@ -10,6 +11,7 @@
 #include <type_traits>
 #include <utility>
 #include <string>
+#include <system_error>
 #include <vector>
 
 #include "../../include/cfr.h"
@@ -134,6 +136,7 @@ struct Sizes {
     int32_t players = 0;     // general-sum game of n rational players (node engine), else 0
     bool level_pure = true;
     bool resident = false;   // small game: the resident iteration's records and state as well
+    bool forest = false;     // a batch of n_games
     // node engine: regret contributions may be stored per child and gathered per infoset (false:
     // always added by atomics, for the partitioned iteration's windows)
     bool gather = true;
@@ -161,13 +164,16 @@ int choose_engine(bool level_pure, int32_t max_actions, uint32_t flags) {
 
 cfr::ResSizes resident_sizes(const Sizes& z) {
     cfr::ResSizes r;
-    r.nodes = z.N; r.decision = z.N - z.terminals; r.members = z.M; r.infosets = z.Hp;
-    r.pairs = z.Qp; r.chance_pairs = z.Q0; r.depth = z.D; r.max_actions = z.max_actions;
+    const int32_t above = z.forest ? 1 : 0;  // a forest's games hang from a node of their own
+    r.nodes = z.N + above; r.decision = z.N - z.terminals + above; r.members = z.M;
+    r.infosets = z.Hp; r.pairs = z.Qp; r.chance_pairs = z.Q0 + above * z.n_games;
+    r.depth = z.D + above; r.max_actions = z.max_actions;
     r.players = z.players; r.real_bytes = z.fp64 ? 8 : 4; r.level_pure = z.level_pure;
+    r.forest = z.forest;
     return r;
 }
 
-// Whether a single game may run resident: its sizes allow it and the configuration asks for none of
+// Whether a game or a forest may run resident: its sizes allow it and the configuration asks for none of
 // the level-by-level launches (direct launches, subtree packs, or for a two-player game the node
 // engine by name).
 bool choose_resident(const Sizes& z, uint32_t flags) {
@@ -181,12 +187,12 @@ template <class F>
 void carve_resident(Carve& c, cfr::Resident<F>& r, const cfr::DevT<F>& d, const Sizes& z) {
     r = cfr::Resident<F>{};
     if (!z.resident) return;
-    const int64_t nd = z.N - z.terminals;
-    const int64_t cols = z.players > 0 ? z.players : 1, planes = z.players > 0 ? z.players : 2;
     const cfr::ResSizes rz = resident_sizes(z);
+    const int64_t N = rz.nodes, nd = rz.decision;
+    const int64_t cols = z.players > 0 ? z.players : 1, planes = z.players > 0 ? z.players : 2;
     const int64_t roots = cfr::resident_max_roots(rz);
-    r.N = z.N; r.ND = static_cast<int32_t>(nd); r.Hp = static_cast<int32_t>(z.Hp);
-    r.Qp = static_cast<int32_t>(z.Qp); r.Q0 = static_cast<int32_t>(z.Q0); r.D = z.D;
+    r.N = N; r.ND = static_cast<int32_t>(nd); r.Hp = static_cast<int32_t>(z.Hp);
+    r.Qp = static_cast<int32_t>(z.Qp); r.Q0 = static_cast<int32_t>(rz.chance_pairs); r.D = rz.depth;
     r.players = z.players;
     r.rec = c.take<cfr::Rec4>(nd);
     r.slot = c.take<int32_t>(nd);
@@ -198,8 +204,8 @@ void carve_resident(Carve& c, cfr::Resident<F>& r, const cfr::DevT<F>& d, const 
     r.table = c.take<cfr::Rec4>(cfr::resident_max_table(rz));
     r.con = c.take<F>(z.M * cfr::res_stride(z.max_actions, sizeof(F)));
     r.root_val = c.take<F>(cols * roots);
-    r.pay = c.take<F>(cols * (z.N + roots));
-    r.val = c.take<F>(cols * (z.N + roots));
+    r.pay = c.take<F>(cols * (N + roots));
+    r.val = c.take<F>(cols * (N + roots));
     r.reach = c.take<F>(planes * nd);
     r.team = c.take<cfr::ResTeam>(1);
     r.prob = d.prob; r.R = d.R; r.S = d.S; r.T = d.T;
@@ -285,7 +291,8 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         return (c.off + 255) & ~size_t{255};
     }
     d.payoff = c.take<float>(cols * N);
-    d.prob = c.take<float>(Qp + Q0);
+    // (and 1 for each edge to a game of a resident forest)
+    d.prob = c.take<float>(Qp + Q0 + (z.forest && z.resident ? z.n_games : 0));
     d.R = c.take<float>(Qp);
     d.S = c.take<float>(Qp);
     d.value = c.take<float>(cols * N);
@@ -890,6 +897,35 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     if (bytes < need)
         return set_err(CFR_ENOMEM, "workspace has " + std::to_string(bytes) + " bytes, needs " +
                                        std::to_string(need));
+    // the resident records are planned beside the uploads of everything else
+    cfr::ResPlan rp;
+    std::vector<float> reach_c32, res_pay32;
+    std::vector<double> res_pay64;
+    const auto plan_records = [&] {
+        std::vector<int32_t> q_of(L.q_offset.begin(), L.q_offset.begin() + L.Hp);
+        if (z.engine == ENGINE_BLOCK)
+            for (int64_t e = 0; e < L.Hp; ++e) q_of[P.infoset_canon[e]] = P.q_offset[e];
+        if (!cfr::build_resident(L, q_of, resident_sizes(z), rp)) return false;
+        if (!fp64) reach_c32.assign(rp.reach_c.begin(), rp.reach_c.end());
+        // payoffs in the bins' order
+        const auto in_bins = [&](const auto& pay, auto& out) {
+            const int64_t nb = static_cast<int64_t>(rp.node.size()), cols = players > 0 ? players : 1;
+            out.resize(cols * nb);
+            for (int64_t c = 0; c < cols; ++c)
+                cfr::for_ranges(nb, [&](int64_t i0, int64_t i1) {
+                    for (int64_t i = i0; i < i1; ++i) out[c * nb + i] = pay[c * L.N + rp.node[i]];
+                });
+        };
+        if (fp64) in_bins(players > 0 ? pay64 : L.payoff64, res_pay64);
+        else in_bins(players > 0 ? pay32 : L.payoff, res_pay32);
+        return true;
+    };
+    std::future<bool> records;  // (waits in its destructor)
+    if (z.resident) try {
+            records = std::async(std::launch::async, plan_records);
+        } catch (const std::system_error&) {  // no thread: planned below
+        }
+    const auto plan_resident = [&] { return records.valid() ? records.get() : plan_records(); };
     auto* s = new cfr_solver();
     carve(d, d64, x, workspace, z, &s->res32, &s->res64);
     s->dev = d;
@@ -967,34 +1003,16 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     if (fp64) cfr::launch_reset(d64, st, true);
     else cfr::launch_reset(d, st, s->engine == ENGINE_NODE);
     if (s->engine == ENGINE_BLOCK) cfr::launch_x_reset(s->xdev, st);
-    cfr::ResPlan rp;
-    std::vector<float> reach_c32, res_pay32;
-    std::vector<double> res_pay64;
+    if (s->resident) s->resident = plan_resident();
     if (s->resident) {
-        std::vector<int32_t> q_of(L.q_offset.begin(), L.q_offset.begin() + L.Hp);
-        if (s->engine == ENGINE_BLOCK)
-            for (int64_t e = 0; e < L.Hp; ++e) q_of[P.infoset_canon[e]] = P.q_offset[e];
-        s->resident = cfr::build_resident(L, q_of, resident_sizes(z), rp);
-    }
-    if (s->resident) {
-        if (!fp64) reach_c32.assign(rp.reach_c.begin(), rp.reach_c.end());
-        // payoffs in the bins' order
-        const auto in_bins = [&](const auto& pay, auto& out) {
-            const int64_t nb = static_cast<int64_t>(rp.node.size()), cols = players > 0 ? players : 1;
-            out.resize(cols * nb);
-            for (int64_t c = 0; c < cols; ++c)
-                for (int64_t i = 0; i < nb; ++i) out[c * nb + i] = pay[c * L.N + rp.node[i]];
-        };
-        if (fp64) in_bins(players > 0 ? pay64 : L.payoff64, res_pay64);
-        else in_bins(players > 0 ? pay32 : L.payoff, res_pay32);
         rc = fp64 ? upload_resident(s->res64, rp, rp.reach_c, res_pay64, st)
                   : upload_resident(s->res32, rp, reach_c32, res_pay32, st);
         if (rc != CFR_OK) {
             discard(s);
             return rc;
         }
-        s->res_node = rp.node;
-        s->res_rank_node = rp.rank_node;
+        s->res_node = std::move(rp.node);
+        s->res_rank_node = std::move(rp.rank_node);
     }
     if ((rc = check_hip("reset")) != CFR_OK) {
         discard(s);
@@ -1845,6 +1863,8 @@ int cfr_plan_batch(const cfr_game* games, int32_t n_games, const cfr_config* con
         z.terminals += L.n_terminals;
     }
     z.packs = z.max_actions <= 4 && config != nullptr && (config->flags & CFR_FLAG_SUBTREE_PACKS);
+    z.forest = true;
+    z.resident = choose_resident(z, config != nullptr ? config->flags : 0);
     cfr::Dev d{};
     cfr::Dev64 d64{};
     cfr::XDev x{};
@@ -1878,8 +1898,13 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     std::string err;
     std::vector<cfr::ExecPlan> plans;
     int32_t max_actions = 0;
+    // the layouts are kept where the batch may run resident: its values alone must fit the LDS
+    int64_t nodes = 0;
+    for (int32_t g = 0; g < n_games; ++g) nodes += std::max<int64_t>(games[g].n_nodes, 0);
+    std::vector<cfr::Layout> layouts;
+    const bool small = nodes * 2 * int64_t{sizeof(float)} <= cfr::kResLds * cfr::kResTeam;
     int rc = cfr::plan_games(games, n_games, plans, max_actions, err,
-                             (cfg.flags & CFR_FLAG_SUBTREE_PACKS) != 0);
+                             (cfg.flags & CFR_FLAG_SUBTREE_PACKS) != 0, small ? &layouts : nullptr);
     if (rc != CFR_OK) return set_err(rc, err);
     cfr::ExecPlan F;
     rc = cfr::build_forest_plan(plans, F, err);
@@ -1894,6 +1919,8 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     z.canonical = false;
     z.n_games = n_games;
     z.packs = max_actions <= 4 && (cfg.flags & CFR_FLAG_SUBTREE_PACKS);
+    z.forest = true;
+    z.resident = choose_resident(z, cfg.flags);
     cfr::Dev d{};
     cfr::Dev64 d64{};
     cfr::XDev x{};
@@ -1903,8 +1930,8 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     if (bytes < need)
         return set_err(CFR_ENOMEM, "workspace has " + std::to_string(bytes) + " bytes, needs " +
                                        std::to_string(need));
-    carve(d, d64, x, workspace, z);
     auto* s = new cfr_solver();
+    carve(d, d64, x, workspace, z, &s->res32);
     s->dev = d;
     s->xdev = x;
     s->engine = ENGINE_BLOCK;
@@ -1919,6 +1946,7 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     hipStream_t st = s->stream;
     std::vector<float> prob_tail(F.Qp + F.Q0, 0.0f);
     std::copy(F.chance_prob.begin(), F.chance_prob.end(), prob_tail.begin() + F.Qp);
+    if (z.resident) prob_tail.resize(F.Qp + F.Q0 + n_games, 1.0f);
     cfr_default_launch_shape(&s->shape);
     if ((rc = upload_plan(s, F, st)) || (rc = upload(d.prob, prob_tail, st))) {
         discard(s);
@@ -1926,6 +1954,31 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     }
     cfr::launch_reset(d, st, false);
     cfr::launch_x_reset(s->xdev, st);
+    cfr::ResPlan rp;
+    std::vector<float> reach_c, pay;
+    if (z.resident) {
+        const cfr::Layout L = cfr::forest_layout(layouts);
+        // each infoset's pairs in the plan: by the input pair of its first
+        std::vector<int32_t> pair_of(F.Qp), q_of(F.Hp);
+        for (int64_t q = 0; q < F.Qp; ++q) pair_of[F.q_input[q]] = static_cast<int32_t>(q);
+        int64_t h = 0, in = 0;
+        for (const cfr::Layout& G : layouts) {
+            for (int64_t i = 0; i < G.Hp; ++i) q_of[h++] = pair_of[in + G.q_input[G.q_offset[i]]];
+            in += G.Qp;
+        }
+        s->resident = cfr::build_resident(L, q_of, resident_sizes(z), rp);
+        pay.resize(rp.node.size());
+        cfr::for_ranges(static_cast<int64_t>(pay.size()), [&](int64_t i0, int64_t i1) {
+            for (int64_t i = i0; i < i1; ++i) pay[i] = L.payoff[rp.node[i]];
+        });
+    }
+    if (s->resident) {
+        reach_c.assign(rp.reach_c.begin(), rp.reach_c.end());
+        if ((rc = upload_resident(s->res32, rp, reach_c, pay, st)) != CFR_OK) {
+            discard(s);
+            return rc;
+        }
+    }
     if ((rc = check_hip("reset")) != CFR_OK) {
         discard(s);
         return rc;
@@ -1939,7 +1992,7 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
         discard(s);
         return rc;
     }
-    if (s->use_graph && (rc = capture(s)) != CFR_OK) {
+    if (s->use_graph && !s->resident && (rc = capture(s)) != CFR_OK) {
         discard(s);
         return rc;
     }
