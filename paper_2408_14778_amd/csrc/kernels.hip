@@ -8,6 +8,8 @@
 // column), and the node -> infoset-action reductions are fused into the bottom-up pass.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace cfr {
@@ -137,16 +139,14 @@ __global__ void k_reach_level(int32_t lo, int32_t hi, int64_t N, const int32_t* 
 // per-infoset accumulators by atomics (the partitioned iteration, whose windows are overwritten
 // partition by partition, accumulates across them this way).
 template <class F, bool kStore>
-__global__ void k_value_level(int32_t lo, int32_t hi, int64_t N,
-                              const int32_t* __restrict__ child_begin,
-                              const int8_t* __restrict__ node_player,
-                              const int32_t* __restrict__ node_infoset,
-                              const int32_t* __restrict__ node_edge,
-                              const F* __restrict__ prob, F* __restrict__ value,
-                              const F* __restrict__ reach, F* __restrict__ rtilde,
-                              F* __restrict__ pibar, F* __restrict__ contrib) {
-    const int64_t p = lo + gid();
-    if (p >= hi) return;
+__device__ __forceinline__ void value_node(int64_t p, int64_t N,
+                                           const int32_t* __restrict__ child_begin,
+                                           const int8_t* __restrict__ node_player,
+                                           const int32_t* __restrict__ node_infoset,
+                                           const int32_t* __restrict__ node_edge,
+                                           const F* __restrict__ prob, F* value,
+                                           const F* __restrict__ reach, F* __restrict__ rtilde,
+                                           F* __restrict__ pibar, F* __restrict__ contrib) {
     const int8_t who = node_player[p];
     if (who < 0) return;
     const int32_t c0 = child_begin[p], c1 = child_begin[p + 1];
@@ -172,6 +172,74 @@ __global__ void k_value_level(int32_t lo, int32_t hi, int64_t N,
     for (int32_t c = c0; c < c1; ++c)
         unsafeAtomicAdd(&rtilde[node_edge[c]], w * (value[c] - u));
     unsafeAtomicAdd(&pibar[h], who == 1 ? r1 : r2);
+}
+
+template <class F, bool kStore>
+__global__ void k_value_level(int32_t lo, int32_t hi, int64_t N,
+                              const int32_t* __restrict__ child_begin,
+                              const int8_t* __restrict__ node_player,
+                              const int32_t* __restrict__ node_infoset,
+                              const int32_t* __restrict__ node_edge,
+                              const F* __restrict__ prob, F* value, const F* __restrict__ reach,
+                              F* __restrict__ rtilde, F* __restrict__ pibar,
+                              F* __restrict__ contrib) {
+    const int64_t p = lo + gid();
+    if (p < hi)
+        value_node<F, kStore>(p, N, child_begin, node_player, node_infoset, node_edge, prob, value,
+                              reach, rtilde, pibar, contrib);
+}
+
+// The out-of-core iteration's resident levels, which are small, in few launches. Top-down: every
+// decision node of the levels walks up to the root and multiplies the edges on its path (with a T it
+// also counts the iteration, ahead of the infoset update that reads it). Bottom-up: the shallowest
+// levels in one workgroup, a barrier between them. 3,309,121 nodes cut at level 7: 7 + 7 launches
+// and the count, 73 us of an iteration, became 1 + 3.
+template <class F>
+__global__ void k_reach_path(int64_t lo, int64_t hi, int64_t N, const int32_t* __restrict__ parent,
+                             const int8_t* __restrict__ node_player,
+                             const int32_t* __restrict__ node_edge, const F* __restrict__ prob,
+                             F* __restrict__ reach, int64_t* T) {
+    if (T != nullptr && gid() == 0) *T += 1;
+    const int64_t v = lo + gid();
+    if (v >= hi || node_player[v] < 0) return;
+    F r1 = F(1), r2 = F(1), rc = F(1);
+    for (int32_t y = static_cast<int32_t>(v); y > 0;) {
+        const int32_t p = parent[y];
+        const F s = prob[node_edge[y]];
+        const int8_t who = node_player[p];
+        if (who == 1) r1 *= s;
+        else if (who == 2) r2 *= s;
+        else rc *= s;
+        y = p;
+    }
+    reach[v] = r1;
+    reach[N + v] = r2;
+    reach[2 * N + v] = rc;
+}
+
+constexpr int kTopLevels = 24;    // levels of one launch of k_value_top, and of a path
+constexpr int32_t kTopNodes = 1024;  // nodes of one of its levels: one pass of its workgroup
+struct TopLevels {
+    int32_t n;                   // levels n - 1 .. 0
+    int32_t lo[kTopLevels + 1];  // their first nodes
+};
+
+template <class F>
+__global__ void __launch_bounds__(kTopNodes) k_value_top(TopLevels t, int64_t N,
+                                                         const int32_t* __restrict__ child_begin,
+                                                         const int8_t* __restrict__ node_player,
+                                                         const int32_t* __restrict__ node_infoset,
+                                                         const int32_t* __restrict__ node_edge,
+                                                         const F* __restrict__ prob, F* value,
+                                                         const F* __restrict__ reach,
+                                                         F* __restrict__ rtilde, F* __restrict__ pibar) {
+    for (int32_t l = t.n - 1; l >= 0; --l) {
+        const int32_t p = t.lo[l] + static_cast<int32_t>(threadIdx.x);
+        if (p < t.lo[l + 1])
+            value_node<F, false>(p, N, child_begin, node_player, node_infoset, node_edge, prob, value,
+                                 reach, rtilde, pibar, nullptr);
+        __syncthreads();
+    }
 }
 
 // ---- general-sum games of P rational players (Section 3.1: the payoff matrix and the
@@ -452,11 +520,11 @@ __global__ void k_infoset_update(int64_t Hp, const int32_t* __restrict__ q_offse
                                  F* __restrict__ R, F* __restrict__ S,
                                  F* __restrict__ sigma, F* __restrict__ rtilde,
                                  F* __restrict__ pibar, const int64_t* __restrict__ T,
-                                 UpdateRule rule) {
+                                 int32_t t_add, UpdateRule rule) {
     const int64_t h = gid();
     if (h >= Hp) return;
     const int32_t o = q_offset[h], k = q_offset[h + 1] - o;
-    const F t = static_cast<F>(*T + 1);
+    const F t = static_cast<F>(*T + t_add);  // (0: the iteration has been counted already)
     F wt = rule.linear ? t : F(1);
     F d_pos = F(1), d_neg = F(1), d_avg = F(1);
     if (rule.variant == 2) {
@@ -768,6 +836,12 @@ void launch_gather(const DevT<F>& d, hipStream_t st) {
     else launch_gather_w<F, 4>(d, st);
 }
 
+// The node range [lo, hi) of one level: top-down reach, bottom-up values with the accumulation.
+template <class F>
+static void launch_reach_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st);
+template <class F>
+static void launch_value_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st);
+
 template <class F>
 void launch_iteration(const DevT<F>& d, const int32_t* lo, const UpdateRule& rule, hipStream_t st,
                       LaunchTimer* timer) {
@@ -792,7 +866,7 @@ void launch_iteration(const DevT<F>& d, const int32_t* lo, const UpdateRule& rul
         launch_gather(d, st);
         hipLaunchKernelGGL(k_infoset_update<F>, dim3(blocks_for(d.Hp)), dim3(kBlock), 0, st, d.Hp,
                            d.q_offset, d.infoset_player, d.R, d.S, d.prob, d.rtilde, d.pibar, d.T,
-                           rule);
+                           1, rule);
         post(K_INFOSET);
     }
     if (rule.count) {
@@ -803,7 +877,7 @@ void launch_iteration(const DevT<F>& d, const int32_t* lo, const UpdateRule& rul
 }
 
 template <class F>
-void launch_reach_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st) {
+static void launch_reach_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st) {
     if (hi <= lo) return;
     if (d.players > 0)
         hipLaunchKernelGGL(k_reach_level_n<F>, dim3(blocks_for(hi - lo)), dim3(kBlock), 0, st, lo,
@@ -815,7 +889,7 @@ void launch_reach_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st
 }
 
 template <class F>
-void launch_value_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st) {
+static void launch_value_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st) {
     if (hi <= lo) return;
     if (d.players > 0 && hi - lo <= kWideTop)
         hipLaunchKernelGGL((k_value_wide_n<F, 16>), dim3(static_cast<unsigned>(hi - lo)), dim3(1024),
@@ -840,13 +914,38 @@ void launch_value_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st
 }
 
 template <class F>
-void launch_infoset_pass(const DevT<F>& d, const UpdateRule& rule, hipStream_t st) {
+bool launch_top_reach(const DevT<F>& d, const int32_t* lo, int32_t last, int64_t* T,
+                      hipStream_t st) {
+    if (last >= 1 && path_applies(lo[last + 1], last)) {
+        hipLaunchKernelGGL(k_reach_path<F>, dim3(blocks_for(lo[last + 1] - lo[1])), dim3(kBlock), 0,
+                           st, int64_t{lo[1]}, int64_t{lo[last + 1]}, d.N, d.parent, d.node_player,
+                           d.node_edge, d.prob, d.reach, T);
+        return T != nullptr;
+    }
+    for (int32_t l = 1; l <= last; ++l) launch_reach_range(d, lo[l], lo[l + 1], st);
+    return false;
+}
+
+template <class F>
+void launch_top_values(const DevT<F>& d, const int32_t* lo, int32_t levels, hipStream_t st) {
+    TopLevels t{};
+    while (t.n < std::min(levels, kTopLevels) && lo[t.n + 1] - lo[t.n] <= kTopNodes) ++t.n;
+    for (int32_t l = levels - 1; l >= t.n; --l) launch_value_range(d, lo[l], lo[l + 1], st);
+    if (t.n == 0) return;
+    std::copy(lo, lo + t.n + 1, t.lo);
+    hipLaunchKernelGGL(k_value_top<F>, dim3(1), dim3(kTopNodes), 0, st, t, d.N, d.child_begin,
+                       d.node_player, d.node_infoset, d.node_edge, d.prob, d.value, d.reach, d.rtilde,
+                       d.pibar);
+}
+
+template <class F>
+void launch_infoset_pass(const DevT<F>& d, const UpdateRule& rule, bool counted, hipStream_t st) {
     launch_gather(d, st);
     if (d.Hp > 0)
         hipLaunchKernelGGL(k_infoset_update<F>, dim3(blocks_for(d.Hp)), dim3(kBlock), 0, st, d.Hp,
                            d.q_offset, d.infoset_player, d.R, d.S, d.prob, d.rtilde, d.pibar, d.T,
-                           rule);
-    if (rule.count) hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, st, d.T);
+                           counted ? 0 : 1, rule);
+    if (rule.count && !counted) hipLaunchKernelGGL(k_tick, dim3(1), dim3(64), 0, st, d.T);
 }
 
 template <class F>
@@ -859,7 +958,7 @@ void launch_average(const DevT<F>& d, hipStream_t st) {
 template <class F>
 void launch_best_response(const DevT<F>& d, const int32_t* lo, const int32_t* hlo, double* out,
                           hipStream_t st) {
-    if (d.D > 1 && br_path_applies(d.N, d.D)) {
+    if (d.D > 1 && path_applies(d.N, d.D)) {
         hipLaunchKernelGGL(k_br_reach_path<F>, dim3(blocks_for(lo[d.D])), dim3(kBlock), 0, st,
                            int64_t{lo[d.D]}, d.N, d.parent, d.node_player, d.node_edge, d.avgprob,
                            d.br_reach);
@@ -908,9 +1007,10 @@ void launch_gather_q(const DevT<F>& d, const F* src, F* dst, hipStream_t st) {
     template void launch_iteration<F>(const DevT<F>&, const int32_t*, const UpdateRule&,       \
                                       hipStream_t, LaunchTimer*);                              \
     template void launch_average<F>(const DevT<F>&, hipStream_t);                              \
-    template void launch_reach_range<F>(const DevT<F>&, int32_t, int32_t, hipStream_t);        \
-    template void launch_value_range<F>(const DevT<F>&, int32_t, int32_t, hipStream_t);        \
-    template void launch_infoset_pass<F>(const DevT<F>&, const UpdateRule&, hipStream_t);      \
+    template void launch_infoset_pass<F>(const DevT<F>&, const UpdateRule&, bool, hipStream_t);\
+    template bool launch_top_reach<F>(const DevT<F>&, const int32_t*, int32_t, int64_t*,       \
+                                      hipStream_t);                                            \
+    template void launch_top_values<F>(const DevT<F>&, const int32_t*, int32_t, hipStream_t);  \
     template void launch_best_response<F>(const DevT<F>&, const int32_t*, const int32_t*,      \
                                           double*, hipStream_t);                               \
     template void launch_scatter_q<F>(const DevT<F>&, const F*, F*, hipStream_t);              \

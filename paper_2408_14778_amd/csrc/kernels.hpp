@@ -138,15 +138,18 @@ __device__ __forceinline__ void dcfr_discounts(const UpdateRule& u, double t, do
 template <class F>
 void launch_iteration(const DevT<F>& d, const int32_t* level_offset_host, const UpdateRule& rule,
                       hipStream_t st, LaunchTimer* timer = nullptr);
-// The parts of one iteration on a node range [lo, hi) of one level (the partitioned iteration
-// composes them): top-down reach, bottom-up values with the regret and own-reach accumulation;
-// then the infoset pass over every infoset (and T += 1 if rule.count).
+// The parts of one iteration that the partitioned one composes: the top-down reach of levels 1 .. last
+// (with a T the iteration may be counted there: true), the bottom-up values of levels `levels` - 1 ..
+// 0 with the regret and own-reach accumulation, and the infoset pass over every infoset (counted:
+// T holds the iteration already; else T += 1 follows if rule.count).
 template <class F>
-void launch_reach_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st);
+bool launch_top_reach(const DevT<F>& d, const int32_t* level_offset_host, int32_t last, int64_t* T,
+                      hipStream_t st);
 template <class F>
-void launch_value_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st);
+void launch_top_values(const DevT<F>& d, const int32_t* level_offset_host, int32_t levels,
+                       hipStream_t st);
 template <class F>
-void launch_infoset_pass(const DevT<F>& d, const UpdateRule& rule, hipStream_t st);
+void launch_infoset_pass(const DevT<F>& d, const UpdateRule& rule, bool counted, hipStream_t st);
 // Average strategy into d.avgprob (canonical order; chance tail copied at reset).
 template <class F>
 void launch_average(const DevT<F>& d, hipStream_t st);
@@ -154,10 +157,10 @@ void launch_average(const DevT<F>& d, hipStream_t st);
 template <class F>
 void launch_best_response(const DevT<F>& d, const int32_t* level_offset_host,
                           const int32_t* infoset_level_offset_host, double* out, hipStream_t st);
-// Whether a best response takes every level's reach in one launch of walks to the root (measured per
-// check: 2.6 million nodes of 15 levels 17 us against 49 us in 14 launches). The walks' work grows
-// with nodes times depth, the launches they replace with the depth alone.
-inline bool br_path_applies(int64_t nodes, int32_t depth) { return nodes <= 4000000 && depth <= 24; }
+// Whether reaches are taken in one launch of walks to the root (measured per check: 2.6 million nodes
+// of 15 levels 17 us against 49 us in 14 launches). The walks' work grows with nodes times depth, the
+// launches they replace with the depth alone.
+inline bool path_applies(int64_t nodes, int32_t depth) { return nodes <= 4000000 && depth <= 24; }
 // dst[q_input[q]] = src[q]  (canonical -> input order)
 template <class F>
 void launch_scatter_q(const DevT<F>& d, const F* src, F* dst, hipStream_t st);

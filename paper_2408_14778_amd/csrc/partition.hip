@@ -318,7 +318,7 @@ void launch_partitioned_pass(const DevT<F>& d, const PartDev<F>& Pd, const Updat
                  d.infoset_player};
     auto blocks = [](int32_t n) { return dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads)); };
     // resident top-down: levels 1 .. cut
-    for (int32_t l = 1; l <= cut; ++l) launch_reach_range(d, lo[l], lo[l + 1], st);
+    const bool counted = launch_top_reach(d, lo, cut, rule.count ? d.T : nullptr, st);
     for (int32_t g = 0; g < P.groups; ++g) {
         // (stream order keeps a group's use of the window after the group before it)
         const size_t at = static_cast<size_t>(g) * nl;
@@ -341,9 +341,8 @@ void launch_partitioned_pass(const DevT<F>& d, const PartDev<F>& Pd, const Updat
                                    Pd.h_child + P.rec[at + i], d.prob, d.value, d.reach, d.rtilde,
                                    d.pibar);
     }
-    // resident bottom-up: levels cut - 1 .. 0
-    for (int32_t l = cut - 1; l >= 0; --l) launch_value_range(d, lo[l], lo[l + 1], st);
-    launch_infoset_pass(d, rule, st);
+    launch_top_values(d, lo, cut, st);  // resident bottom-up: levels cut - 1 .. 0
+    launch_infoset_pass(d, rule, counted, st);
 }
 
 template struct PartDev<float>;

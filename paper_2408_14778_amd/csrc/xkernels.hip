@@ -1027,7 +1027,7 @@ __global__ void k_x_br_reach(int32_t lo, int32_t hi, int64_t N, const int32_t* _
 }
 
 // Every level in one launch: each decision node of lo .. hi - 1 walks up to its root (nodes below
-// n_roots) and multiplies the edges on its path (br_path_applies says when).
+// n_roots) and multiplies the edges on its path (path_applies says when).
 __global__ void __launch_bounds__(256) k_x_br_reach_path(int32_t lo, int32_t hi, int32_t n_roots,
                                                          int64_t N,
                                                          const int32_t* __restrict__ parent,
@@ -1603,7 +1603,7 @@ void launch_br_cap(const XDev& x, const BrArgs& a, int32_t l, hipStream_t st) {
 
 void launch_x_best_response(const XDev& x, const float* avgprob, double* out, hipStream_t st) {
     const int32_t* lo = x.level_offset_host;
-    if (x.D > 1 && br_path_applies(x.N, x.D))
+    if (x.D > 1 && path_applies(x.N, x.D))
         hipLaunchKernelGGL(k_x_br_reach_path, dim3(blocks_of(lo[x.D] - lo[1], kBlock)), dim3(kBlock), 0,
                            st, lo[1], lo[x.D], lo[1], x.N, x.parent, x.edge, x.meta, avgprob,
                            x.br_reach);
