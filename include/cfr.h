@@ -21,8 +21,8 @@
  *  - Host arrays passed in are borrowed for the duration of the call and
  *    copied; the library keeps no pointer to them.
  *  - Device memory: the caller owns the workspace (cfr_plan reports its
- *    size); the solver lives inside it and owns only host metadata, events and
- *    the captured iteration graph. The workspace must stay allocated until
+ *    size); the solver lives inside it and owns only host metadata, events,
+ *    the captured iteration graph and a few pinned words for its results. The workspace must stay allocated until
  *    cfr_destroy returns.
  *  - Streams: all GPU work of a solver is ordered on the hipStream_t given to
  *    cfr_build (may be the null stream).
@@ -83,7 +83,9 @@ enum { CFR_AVG_DEFAULT = -1, CFR_AVG_UNIFORM = 0, CFR_AVG_LINEAR = 1 };
  * (linear). DEFAULT = uniform for vanilla, linear for CFR+; CFR_DCFR takes DEFAULT only (its
  * gamma discount sets the weights). */
 
-#define CFR_FLAG_NO_GRAPH 1u    /* enqueue kernels directly instead of replaying a captured graph */
+#define CFR_FLAG_NO_GRAPH 1u    /* enqueue the level-by-level kernels directly instead of replaying a
+                                    captured graph or, for a game small enough, running whole
+                                    iterations in one launch (cfr_iterate) */
 #define CFR_FLAG_NODE_ENGINE 2u  /* use the breadth-first node engine even where the public-block
                                     engine applies (level-pure infosets, at most 16 actions) */
 #define CFR_FLAG_ALTERNATING 4u  /* alternating updates (the schedule of the cited CFR+ work): an
@@ -144,7 +146,12 @@ int cfr_plan(const cfr_game* game, const cfr_config* config, cfr_plan_info* out)
 int cfr_build(const cfr_game* game, const cfr_config* config, void* workspace, size_t bytes,
               void* stream, cfr_solver** out);
 
-/* Enqueue n iterations (Section 3.2) on the solver's stream; does not synchronise. */
+/* Enqueue n iterations (Section 3.2) on the solver's stream; does not synchronise. A game whose
+ * subtrees fit the LDS of the chip's CUs a few times over (in single precision up to about 7 million
+ * nodes; a batch up to about 2 million) runs all n in one launch, unless the configuration asks for the
+ * level-by-level kernels (CFR_FLAG_NO_GRAPH, CFR_FLAG_SUBTREE_PACKS, CFR_FLAG_KEEP_NODE_VALUES, or for
+ * two players CFR_FLAG_NODE_ENGINE) or the workspace has room for those alone; any other game replays
+ * its captured iteration n times. Two-player single-precision results are the same bit for bit. */
 int cfr_iterate(cfr_solver* s, int32_t n);
 
 /* Run n iterations with direct launches and a pair of hipEvents around every kernel launch on
@@ -334,7 +341,8 @@ int cfr_host_layout_create_batch(const cfr_game* games, int32_t n_games, uint32_
 /* Batched solving: n_games independent games (e.g. the subgames of a larger game) solved
  * together. They are laid out as one forest, level-major (level l holds level l of every game,
  * in game order) over the public-block plan, so each level of every game is processed by one
- * launch and one iteration of all games is one graph replay. All games must have level-pure
+ * launch and one iteration of all games is one graph replay (a batch of up to about 2 million
+ * nodes runs its iterations in one launch). All games must have level-pure
  * infosets and at most 16 actions per infoset (CFR_ELEVEL / CFR_EINVAL otherwise). The batch
  * solver accepts cfr_iterate, cfr_iterate_timed, cfr_average_strategy, cfr_current_strategy,
  * cfr_get_state, cfr_set_state and cfr_destroy; infoset-action pairs are numbered by

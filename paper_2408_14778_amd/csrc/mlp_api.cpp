@@ -18,7 +18,8 @@ namespace {
 
 using cfr::offsets;
 
-size_t layout(cfr_mlp& n, void* base, int32_t F, int32_t H, int32_t A, int32_t maxB) {
+size_t layout(cfr_mlp& n, void* base, int32_t F, int32_t H, int32_t A, int32_t maxB,
+              bool fused_train = true) {
     uintptr_t p = reinterpret_cast<uintptr_t>(base);
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -30,13 +31,14 @@ size_t layout(cfr_mlp& n, void* base, int32_t F, int32_t H, int32_t A, int32_t m
     int64_t o[7];
     const int64_t P = offsets(F, H, A, o);
     n.F = F; n.H = H; n.A = A; n.maxB = maxB; n.n_params = P;
+    n.fused_train = fused_train;
     n.w = static_cast<float*>(take(P * 4));
     n.g = static_cast<float*>(take(P * 4));
     n.m = static_cast<float*>(take(P * 4));
     n.v = static_cast<float*>(take(P * 4));
     n.wb = static_cast<__bf16*>(take(P * 2));
     n.wbT = static_cast<__bf16*>(take(P * 2));
-    n.wbP = static_cast<__bf16*>(take((int64_t{F} + 2 * int64_t{H}) * H * 2));
+    n.wbP = static_cast<__bf16*>(take((int64_t{F} + (fused_train ? 2 : 1) * int64_t{H}) * H * 2));
     n.A1 = static_cast<__bf16*>(take(int64_t{maxB} * H * 2));
     n.A2 = static_cast<__bf16*>(take(int64_t{maxB} * H * 2));
     n.dZ2 = static_cast<__bf16*>(take(int64_t{maxB} * H * 2));
@@ -49,7 +51,7 @@ size_t layout(cfr_mlp& n, void* base, int32_t F, int32_t H, int32_t A, int32_t m
     n.part = static_cast<float*>(
         take(std::max({int64_t{cfr::kMaxSplits} * std::max(F, H) * std::max(H, A),
                        int64_t{cfr::kColsumMaxSplits} * std::max(H, A),
-                       cfr::mlp_train_part_floats(F, H, A)}) * 4));
+                       fused_train ? cfr::mlp_train_part_floats(F, H, A) : 0}) * 4));
     return (off + 255) & ~size_t{255};
 }
 
@@ -88,7 +90,7 @@ void transpose_weights(cfr_mlp* n) {
     cfr::launch_pack_fragments(n->F, n->H, n->wbT + t[0], n->wbP, n->st);
     const int64_t p2 = int64_t{n->F} * n->H, p3 = p2 + int64_t{n->H} * n->H;
     cfr::launch_pack_fragments(n->H, n->H, n->wbT + t[1], n->wbP + p2, n->st);
-    cfr::launch_pack_fragments(n->H, n->H, n->wb + o[2], n->wbP + p3, n->st);
+    if (n->fused_train) cfr::launch_pack_fragments(n->H, n->H, n->wb + o[2], n->wbP + p3, n->st);
 }
 
 }  // namespace
@@ -114,7 +116,9 @@ int cfr_mlp_create(int32_t in_features, int32_t hidden, int32_t outputs, int32_t
         outputs > 32 || max_batch < 1)
         return cfr::set_error(CFR_EINVAL, "bad network shape or null argument");
     auto* n = new cfr_mlp();
-    const size_t need = layout(*n, workspace, in_features, hidden, outputs, max_batch);
+    size_t need = layout(*n, workspace, in_features, hidden, outputs, max_batch);
+    // (a smaller workspace trains layer by layer)
+    if (bytes < need) need = layout(*n, workspace, in_features, hidden, outputs, max_batch, false);
     if (bytes < need) {
         delete n;
         return cfr::set_error(CFR_ENOMEM, "network workspace too small");
@@ -205,7 +209,7 @@ int cfr_mlp_train_step(cfr_mlp* n, const void* x, const float* target, const flo
     ta.w = n->w; ta.g = n->g; ta.m = n->m; ta.v = n->v;
     ta.wb = n->wb; ta.wbT = n->wbT; ta.wbP = n->wbP;
     ta.lr = lr; ta.beta1 = b1; ta.beta2 = b2; ta.eps = eps; ta.c1 = c1; ta.c2 = c2;
-    if (!cfr::launch_mlp_train(B, F, H, A, ta, n->st)) {
+    if (!n->fused_train || !cfr::launch_mlp_train(B, F, H, A, ta, n->st)) {
         forward(n, x, B);
         MLP_TRY(hipMemsetAsync(n->loss, 0, 4, n->st), "loss reset");
         cfr::launch_softmax_xent(B, A, n->Z3, target, mask, n->dZ3, n->loss, n->st);

@@ -24,6 +24,7 @@ struct cfr_mlp {
     float *Z3, *loss;
     float* part;  // partials of the weight and bias gradients
     int64_t step;
+    bool fused_train;  // the workspace has room for the fused training step's weights and partials
     float* h_loss;  // pinned: a step's loss for the caller, written by the kernel in place
 };
 

@@ -893,7 +893,11 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     cfr::Dev d{};
     cfr::Dev64 d64{};
     cfr::XDev x{};
-    const size_t need = carve(d, d64, x, nullptr, z);
+    size_t need = carve(d, d64, x, nullptr, z);
+    if (bytes < need && z.resident) {  // room for the level-by-level launches alone
+        z.resident = false;
+        need = carve(d, d64, x, nullptr, z);
+    }
     if (bytes < need)
         return set_err(CFR_ENOMEM, "workspace has " + std::to_string(bytes) + " bytes, needs " +
                                        std::to_string(need));
@@ -1926,7 +1930,11 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     cfr::XDev x{};
     // cfr_plan_batch bounds the explicit child lists by the node count, so a workspace of the
     // planned size always covers the exact need
-    const size_t need = carve(d, d64, x, nullptr, z);
+    size_t need = carve(d, d64, x, nullptr, z);
+    if (bytes < need && z.resident) {  // room for the level-by-level launches alone
+        z.resident = false;
+        need = carve(d, d64, x, nullptr, z);
+    }
     if (bytes < need)
         return set_err(CFR_ENOMEM, "workspace has " + std::to_string(bytes) + " bytes, needs " +
                                        std::to_string(need));

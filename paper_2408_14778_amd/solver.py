@@ -472,7 +472,8 @@ def plan_partitioned(game, cut_level: int, max_window_nodes: int, variant: str =
 
 
 class BatchSolver(Solver):
-    """Many independent games solved together (one forest, one graph replay per iteration).
+    """Many independent games solved together (one forest; small batches run all iterations of a call
+    in one launch, others one graph replay per iteration).
 
     Pair vectors (state, strategies) concatenate the games' input pair orders, game 0 first;
     ``pair_offsets[g]`` is where game g's pairs start."""
