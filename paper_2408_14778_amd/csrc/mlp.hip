@@ -472,6 +472,8 @@ __device__ __forceinline__ float softmax_xent_row(int B, const float* z, const f
 // same rounding of the hidden layers, the same tree over the last layer's sums (groups l and
 // l ^ 16 first, then ^ 8, ^ 4, ^ 2, ^ 1).
 // F: a multiple of 16 up to kFusedMaxF; H 64, 128 or 256; A <= kNarrow.
+// Bound by the matrix units, fed from LDS and L2: 65,536 rows of 96 -> 256 -> 256 -> 4 take 15.7 to 16.2 us,
+// 740 TFLOP/s, against 42 to 45 us with one wavefront per 32 rows, each reading all the weights.
 constexpr int kFusedMaxF = 128;
 constexpr int kAhead(int rpw) { return rpw >= 4 ? 4 : rpw == 2 ? 8 : 16; }
 
@@ -821,7 +823,8 @@ __global__ void __launch_bounds__(256, TRAIN ? 1 : 2) k_mlp_rows(int M, int F, i
 // columns of one row) and stored to LDS transposed, two rows' values to a 32-bit word, so that
 // the fragments read 8 consecutive k as k_gemm_tile's do; the k-steps and the splits are those
 // of launch_gemm, so every partial equals its. A bias job sums 4 x rps rows of 64 columns, one
-// wavefront per rps rows, as k_colsum_part.
+// wavefront per rps rows, as k_colsum_part. Bound by its loads and the transposition through LDS: 14.5 us
+// for 4,096 rows (a step was 27 launches and 178 us; its three take 40 us, 52 with the caller's wait).
 struct TrainJobs {
     int B, F, H, A;
     const __bf16 *X, *A1, *A2, *dZ1, *dZ2, *dZ3;
@@ -957,7 +960,8 @@ __global__ void __launch_bounds__(256) k_train_grads(TrainJobs q) {
 
 // Adds a step's partials (as k_sum_splits and k_sum_cols), applies Adam (as k_adam) and writes
 // every BF16 copy of the new weights: workgroups [0, nw) one thread per weight, then one
-// wavefront per bias; the last workgroup adds the loss partials in order.
+// wavefront per bias; the last workgroup adds the loss partials in order. Bound by the partials' reads:
+// 6 us at 96 -> 256 -> 256 -> 4.
 __global__ void __launch_bounds__(256) k_train_update(TrainJobs q, int nw, int nl,
                                                       const float* __restrict__ lpart,
                                                       float* __restrict__ loss, float* __restrict__ w,
@@ -1097,7 +1101,8 @@ __global__ void k_to_bf16(int64_t n, const float* __restrict__ src, __bf16* __re
 // Poker-subgame features. Descriptor fields (int16): see mlp.hpp. A workgroup builds kFeatRows
 // rows in LDS (zeroed, then the few non-zero entries written, four threads per row) and stores
 // them with consecutive threads on consecutive 16-byte granules (VEC: F a multiple of 8, X and
-// desc 16-byte aligned; else element by element).
+// desc 16-byte aligned; else element by element). Bound by its stores: 200,001 rows of 96 in 15 us (2.5
+// TB/s; 262 us with a thread per row writing element by element).
 constexpr int kFeatRows = 64;
 constexpr int kFeatLd = 88;  // kFeatures rounded up to granules of 8
 
@@ -1333,6 +1338,12 @@ void with_rows(int M, int F, Go go) {
         if (F == 96) go(k_mlp_rows<H, RT, 6, NA, TRAIN>, grid);
         else go(k_mlp_rows<H, RT, 0, NA, TRAIN>, grid);
     };
+    // Rows per workgroup: more of them share a read of the weights, fewer fill more CUs. The lines lie
+    // where there is a workgroup for each of the 256 CUs (96 -> 256 -> 256 -> 4, forward with 32, 64,
+    // 128 rows: 16,384 rows all within the 9.4 us that a call costs the host, 24,576 rows 12.5, 9.9,
+    // 11.2 us, 32,768 rows 15.1, 11.2, 11.5 us, 65,536 rows 25.7, 18.0, 15.7 us; a training step of
+    // 4,096 rows 52 us with 32, 55 us with 64). Training keeps 64 at most: its backward pass's
+    // accumulators leave no registers for 128.
     if (NA == 4 && !TRAIN && M >= 128 * 256) rows(std::integral_constant<int, NA == 4 && !TRAIN ? 4 : 2>{});
     else if (H == 64 || M >= 64 * 256) rows(std::integral_constant<int, 2>{});
     else rows(std::integral_constant<int, H == 64 ? 2 : 1>{});
@@ -1371,8 +1382,9 @@ int64_t mlp_train_part_floats(int F, int H, int A) {
 }
 
 bool launch_mlp_train(int B, int F, int H, int A, const TrainArgs& t, hipStream_t st) {
-    // (below 64 rows the weight gradients are single short reductions: the per-layer path)
-    if (!mlp_fused_shape(F, H, A, t.x) || B < 64) return false;
+    // (a step of 64 rows, 96 -> 256 -> 256 -> 4: 37 us with the caller's wait against 108 us layer by
+    // layer; of 4,096 rows 52 against 153 us)
+    if (!mlp_fused_shape(F, H, A, t.x)) return false;
     float* p = t.part;
     TrainJobs q{};
     q.B = B; q.F = F; q.H = H; q.A = A;
