@@ -353,6 +353,7 @@ size_t carve(cfr::Dev& d, cfr::Dev64& d64, cfr::XDev& x, void* base, const Sizes
         x.T = d.T;
         x.br_reach = c.take<float>(2 * N);
         x.br_value = c.take<float>(2 * N);
+        if (!z.resident) x.path_tab = c.take<uint32_t>(cfr::kPathDepth * std::min(N, cfr::kPathTable));
         d.sq_offset = x.q_offset;
         d.sq_input = x.q_input;
     }
@@ -773,6 +774,12 @@ int upload_plan(cfr_solver* s, const cfr::ExecPlan& P, hipStream_t st) {
         x.fused_reach = 0;
         x.path_reach = p0;
     }
+    // from the roots it reads a table of paths, where that has room
+    const int64_t path_nodes = x.path_reach > 0 ? x.level_offset_host[x.path_reach + 1] -
+                                                      x.level_offset_host[1] : 0;
+    if (x.fused_reach != 0 || path_nodes == 0 || path_nodes > std::min(P.N, cfr::kPathTable) ||
+        P.Qp + P.Q0 >= int64_t{1} << 30)
+        x.path_tab = nullptr;
     x.fused_up = cfr::fusable_up_levels(x.m_level_offset_host, s->x_m_up_end.data(),
                                         x.h_level_offset_host, x.h_up_end_host,
                                         x.c_level_offset_host, x.c_up_end_host,

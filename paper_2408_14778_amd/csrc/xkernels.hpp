@@ -31,6 +31,7 @@ constexpr int kPathDepth = 7;
 constexpr int kPathDepthBelowTop = 5;
 constexpr int64_t kPathNodes = 200000;
 constexpr int kPathThreads = 256;
+constexpr int64_t kPathTable = 1000000;  // nodes of a path launch's table
 // Byte ranges that a single-workgroup kernel reads, touched once before its level chain (one
 // byte per kWarmLine-byte line, every load in flight together), so that the chain's dependent
 // loads find their lines in the L2 cache of the workgroup's XCD instead of going to memory
@@ -87,6 +88,7 @@ struct XDev {
     // top-down levels fused_reach + 1 .. path_reach run in one path launch (path_reach <=
     // fused_reach: none)
     int32_t path_reach;
+    uint32_t* path_tab;  // the path launch's players' edges (k_x_path_table), or null
     // per level (host): 1 if every upper decision node of the level has only terminal children
     const int8_t* only_terminal_children_host;
     // pair ranges [lo, hi) of prob that the single-workgroup kernels read (host): the infosets'
