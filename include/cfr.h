@@ -147,7 +147,7 @@ int cfr_build(const cfr_game* game, const cfr_config* config, void* workspace, s
               void* stream, cfr_solver** out);
 
 /* Enqueue n iterations (Section 3.2) on the solver's stream; does not synchronise. A game whose
- * subtrees fit the LDS of the chip's CUs a few times over (in single precision up to about 7 million
+ * subtrees fit the LDS of the chip's CUs a few times over (in single precision up to about 6 million
  * nodes; a batch up to about 2 million) runs all n in one launch, unless the configuration asks for the
  * level-by-level kernels (CFR_FLAG_NO_GRAPH, CFR_FLAG_SUBTREE_PACKS, CFR_FLAG_KEEP_NODE_VALUES, or for
  * two players CFR_FLAG_NODE_ENGINE) or the workspace has room for those alone; any other game replays

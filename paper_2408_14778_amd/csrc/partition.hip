@@ -268,7 +268,7 @@ int PartDev<F>::upload() {
     const size_t stream_bytes = static_cast<size_t>(P.words) * sizeof(F);
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_stream_run<F>),
                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                            static_cast<int>(run_lds<F>(P.max_unit))) != hipSuccess)
+                            static_cast<int>(run_lds<F>(kStreamMax))) != hipSuccess)
         return -1;
     if (pinned(&h_stream, static_cast<int64_t>(stream_bytes)) ||
         pinned(&h_units, static_cast<int64_t>(unit_bytes)) ||
