@@ -190,12 +190,12 @@ __global__ void k_value_level(int32_t lo, int32_t hi, int64_t N,
 }
 
 // The out-of-core iteration's resident levels, which are small, in few launches. Top-down: every
-// decision node of the levels walks up to the root and multiplies the edges on its path (with a T it
-// also counts the iteration, ahead of the infoset update that reads it). Bottom-up: the shallowest
+// decision node of lo .. hi - 1 walks up to a node below `stop` and multiplies the edges on its path
+// (walk_groups; with a T it also counts the iteration, ahead of the update that reads it). Bottom-up: the shallowest
 // levels in one workgroup, a barrier between them. 3,309,121 nodes cut at level 7: 7 + 7 launches
 // and the count, 73 us of an iteration, became 1 + 3.
 template <class F>
-__global__ void k_reach_path(int64_t lo, int64_t hi, int64_t N, const int32_t* __restrict__ parent,
+__global__ void k_reach_path(int64_t lo, int64_t hi, int32_t stop, int64_t N, const int32_t* __restrict__ parent,
                              const int8_t* __restrict__ node_player,
                              const int32_t* __restrict__ node_edge, const F* __restrict__ prob,
                              F* __restrict__ reach, int64_t* T) {
@@ -203,7 +203,8 @@ __global__ void k_reach_path(int64_t lo, int64_t hi, int64_t N, const int32_t* _
     const int64_t v = lo + gid();
     if (v >= hi || node_player[v] < 0) return;
     F r1 = F(1), r2 = F(1), rc = F(1);
-    for (int32_t y = static_cast<int32_t>(v); y > 0;) {
+    int32_t y = static_cast<int32_t>(v);
+    while (y >= stop) {
         const int32_t p = parent[y];
         const F s = prob[node_edge[y]];
         const int8_t who = node_player[p];
@@ -212,12 +213,12 @@ __global__ void k_reach_path(int64_t lo, int64_t hi, int64_t N, const int32_t* _
         else rc *= s;
         y = p;
     }
-    reach[v] = r1;
-    reach[N + v] = r2;
-    reach[2 * N + v] = rc;
+    reach[v] = r1 * reach[y];
+    reach[N + v] = r2 * reach[N + y];
+    reach[2 * N + v] = rc * reach[2 * N + y];
 }
 
-constexpr int kTopLevels = 24;    // levels of one launch of k_value_top, and of a path
+constexpr int kTopLevels = 24;       // levels of one launch of k_value_top
 constexpr int32_t kTopNodes = 1024;  // nodes of one of its levels: one pass of its workgroup
 struct TopLevels {
     int32_t n;                   // levels n - 1 .. 0
@@ -585,37 +586,20 @@ __global__ void k_br_setup(int64_t N, const int8_t* __restrict__ node_player,
     if (v == 0) br_reach[0] = br_reach[N] = F(1);
 }
 
-// One level from its parents' reach: chance and player-2 edges for pi_{-1}, chance and player-1
-// edges for pi_{-2} (decision nodes only).
+// Levels lo .. hi - 1 (walk_groups; `stop`: the first node of the first of them): each decision node
+// walks up to a node whose reach is stored, chance and player-2 edges for pi_{-1}, chance and player-1
+// edges for pi_{-2}.
 template <class F>
-__global__ void k_br_reach_level(int32_t lo, int32_t hi, int64_t N,
-                                 const int32_t* __restrict__ parent,
-                                 const int8_t* __restrict__ node_player,
-                                 const int32_t* __restrict__ node_edge,
-                                 const F* __restrict__ avgprob, F* __restrict__ br_reach) {
+__global__ void k_br_reach(int64_t lo, int64_t hi, int32_t stop, int64_t N,
+                           const int32_t* __restrict__ parent,
+                           const int8_t* __restrict__ node_player,
+                           const int32_t* __restrict__ node_edge, const F* __restrict__ avgprob,
+                           F* __restrict__ br_reach) {
     const int64_t v = lo + gid();
-    if (v >= hi) return;
-    if (node_player[v] < 0) return;
-    const int32_t p = parent[v];
-    const F s = avgprob[node_edge[v]];
-    const int8_t who = node_player[p];
-    const F r0 = br_reach[p], r1 = br_reach[N + p];
-    br_reach[v] = who == 1 ? r0 : r0 * s;
-    br_reach[N + v] = who == 2 ? r1 : r1 * s;
-}
-
-// Every level in one launch: each decision node walks up to the root and multiplies the edges on its
-// path. The walk repeats what the levels share, but costs one launch (about 0.3 us per step)
-// instead of one of 3 to 4 us per level.
-template <class F>
-__global__ void k_br_reach_path(int64_t n, int64_t N, const int32_t* __restrict__ parent,
-                                const int8_t* __restrict__ node_player,
-                                const int32_t* __restrict__ node_edge,
-                                const F* __restrict__ avgprob, F* __restrict__ br_reach) {
-    const int64_t v = 1 + gid();
-    if (v >= n || node_player[v] < 0) return;
+    if (v >= hi || node_player[v] < 0) return;
     F r0 = F(1), r1 = F(1);
-    for (int32_t y = static_cast<int32_t>(v); y > 0;) {
+    int32_t y = static_cast<int32_t>(v);
+    while (y >= stop) {
         const int32_t p = parent[y];
         const F s = avgprob[node_edge[y]];
         const int8_t who = node_player[p];
@@ -623,8 +607,8 @@ __global__ void k_br_reach_path(int64_t n, int64_t N, const int32_t* __restrict_
         if (who != 2) r1 *= s;
         y = p;
     }
-    br_reach[v] = r0;
-    br_reach[N + v] = r1;
+    br_reach[v] = r0 * br_reach[y];
+    br_reach[N + v] = r1 * br_reach[N + y];
 }
 
 // a*(h) = argmax_a sum_{d in h} pi_{-i}(d) V_i(child(d, a)), lowest index on ties: one thread per
@@ -914,16 +898,13 @@ static void launch_value_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStre
 }
 
 template <class F>
-bool launch_top_reach(const DevT<F>& d, const int32_t* lo, int32_t last, int64_t* T,
+void launch_top_reach(const DevT<F>& d, const int32_t* lo, int32_t last, int64_t* T,
                       hipStream_t st) {
-    if (last >= 1 && path_applies(lo[last + 1], last)) {
-        hipLaunchKernelGGL(k_reach_path<F>, dim3(blocks_for(lo[last + 1] - lo[1])), dim3(kBlock), 0,
-                           st, int64_t{lo[1]}, int64_t{lo[last + 1]}, d.N, d.parent, d.node_player,
-                           d.node_edge, d.prob, d.reach, T);
-        return T != nullptr;
-    }
-    for (int32_t l = 1; l <= last; ++l) launch_reach_range(d, lo[l], lo[l + 1], st);
-    return false;
+    walk_groups(lo, last, [&](int32_t a, int32_t b) {
+        hipLaunchKernelGGL(k_reach_path<F>, dim3(blocks_for(lo[b] - lo[a])), dim3(kBlock), 0, st,
+                           int64_t{lo[a]}, int64_t{lo[b]}, lo[a], d.N, d.parent, d.node_player,
+                           d.node_edge, d.prob, d.reach, a == 1 ? T : nullptr);
+    });
 }
 
 template <class F>
@@ -958,16 +939,11 @@ void launch_average(const DevT<F>& d, hipStream_t st) {
 template <class F>
 void launch_best_response(const DevT<F>& d, const int32_t* lo, const int32_t* hlo, double* out,
                           hipStream_t st) {
-    if (d.D > 1 && path_applies(d.N, d.D)) {
-        hipLaunchKernelGGL(k_br_reach_path<F>, dim3(blocks_for(lo[d.D])), dim3(kBlock), 0, st,
-                           int64_t{lo[d.D]}, d.N, d.parent, d.node_player, d.node_edge, d.avgprob,
-                           d.br_reach);
-    } else {
-        for (int32_t l = 1; l < d.D; ++l)
-            hipLaunchKernelGGL(k_br_reach_level<F>, dim3(blocks_for(lo[l + 1] - lo[l])), dim3(kBlock), 0,
-                               st, lo[l], lo[l + 1], d.N, d.parent, d.node_player, d.node_edge,
-                               d.avgprob, d.br_reach);
-    }
+    walk_groups(lo, d.D - 1, [&](int32_t a, int32_t b) {
+        hipLaunchKernelGGL(k_br_reach<F>, dim3(blocks_for(lo[b] - lo[a])), dim3(kBlock), 0, st,
+                           int64_t{lo[a]}, int64_t{lo[b]}, lo[a], d.N, d.parent, d.node_player,
+                           d.node_edge, d.avgprob, d.br_reach);
+    });
     for (int32_t l = d.D - 1; l >= 0; --l) {
         const int32_t ha = hlo[l], hb = hlo[l + 1];
         if (hb > ha)
@@ -1008,7 +984,7 @@ void launch_gather_q(const DevT<F>& d, const F* src, F* dst, hipStream_t st) {
                                       hipStream_t, LaunchTimer*);                              \
     template void launch_average<F>(const DevT<F>&, hipStream_t);                              \
     template void launch_infoset_pass<F>(const DevT<F>&, const UpdateRule&, bool, hipStream_t);\
-    template bool launch_top_reach<F>(const DevT<F>&, const int32_t*, int32_t, int64_t*,       \
+    template void launch_top_reach<F>(const DevT<F>&, const int32_t*, int32_t, int64_t*,       \
                                       hipStream_t);                                            \
     template void launch_top_values<F>(const DevT<F>&, const int32_t*, int32_t, hipStream_t);  \
     template void launch_best_response<F>(const DevT<F>&, const int32_t*, const int32_t*,      \

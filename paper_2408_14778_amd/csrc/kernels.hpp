@@ -139,11 +139,11 @@ template <class F>
 void launch_iteration(const DevT<F>& d, const int32_t* level_offset_host, const UpdateRule& rule,
                       hipStream_t st, LaunchTimer* timer = nullptr);
 // The parts of one iteration that the partitioned one composes: the top-down reach of levels 1 .. last
-// (with a T the iteration may be counted there: true), the bottom-up values of levels `levels` - 1 ..
+// (last >= 1; with a T it also counts the iteration), the bottom-up values of levels `levels` - 1 ..
 // 0 with the regret and own-reach accumulation, and the infoset pass over every infoset (counted:
 // T holds the iteration already; else T += 1 follows if rule.count).
 template <class F>
-bool launch_top_reach(const DevT<F>& d, const int32_t* level_offset_host, int32_t last, int64_t* T,
+void launch_top_reach(const DevT<F>& d, const int32_t* level_offset_host, int32_t last, int64_t* T,
                       hipStream_t st);
 template <class F>
 void launch_top_values(const DevT<F>& d, const int32_t* level_offset_host, int32_t levels,
@@ -157,10 +157,25 @@ void launch_average(const DevT<F>& d, hipStream_t st);
 template <class F>
 void launch_best_response(const DevT<F>& d, const int32_t* level_offset_host,
                           const int32_t* infoset_level_offset_host, double* out, hipStream_t st);
-// Whether reaches are taken in one launch of walks to the root (measured per check: 2.6 million nodes
-// of 15 levels 17 us against 49 us in 14 launches). The walks' work grows with nodes times depth, the
-// launches they replace with the depth alone.
-inline bool path_applies(int64_t nodes, int32_t depth) { return nodes <= 4000000 && depth <= 24; }
+// Reaches top-down by walks: f(a, b) for groups of consecutive levels a .. b - 1 of 1 .. last, which one
+// launch takes, each node walking up to the level above the group and multiplying the edges on its
+// way. A walk repeats what the levels share (about 6 us for each million steps), a launch costs 4 to 5
+// us: levels join while their steps stay within kWalkSteps (2.2 million nodes of 15 levels in double
+// precision: one launch 44 us, 3 launches 31 us; 48 games of 10.9 million nodes: 12 launches of a level
+// each 74 us, 6 launches 61 us).
+constexpr int64_t kWalkSteps = 4000000;  // (of all nodes: a third of them decide and walk)
+constexpr int32_t kWalkLevels = 24;
+template <class Fn>
+void walk_groups(const int32_t* level_offset_host, int32_t last, const Fn& f) {
+    for (int32_t a = 1, b; a <= last; a = b) {
+        int64_t steps = 0;
+        for (b = a; b <= last && b - a < kWalkLevels; ++b) {
+            steps += int64_t{level_offset_host[b + 1] - level_offset_host[b]} * (b - a + 1);
+            if (b > a && steps > kWalkSteps) break;
+        }
+        f(a, b);
+    }
+}
 // dst[q_input[q]] = src[q]  (canonical -> input order)
 template <class F>
 void launch_scatter_q(const DevT<F>& d, const F* src, F* dst, hipStream_t st);

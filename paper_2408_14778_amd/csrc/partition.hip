@@ -318,7 +318,7 @@ void launch_partitioned_pass(const DevT<F>& d, const PartDev<F>& Pd, const Updat
                  d.infoset_player};
     auto blocks = [](int32_t n) { return dim3(static_cast<unsigned>((n + kThreads - 1) / kThreads)); };
     // resident top-down: levels 1 .. cut
-    const bool counted = launch_top_reach(d, lo, cut, rule.count ? d.T : nullptr, st);
+    launch_top_reach(d, lo, cut, rule.count ? d.T : nullptr, st);
     for (int32_t g = 0; g < P.groups; ++g) {
         // (stream order keeps a group's use of the window after the group before it)
         const size_t at = static_cast<size_t>(g) * nl;
@@ -342,7 +342,7 @@ void launch_partitioned_pass(const DevT<F>& d, const PartDev<F>& Pd, const Updat
                                    d.pibar);
     }
     launch_top_values(d, lo, cut, st);  // resident bottom-up: levels cut - 1 .. 0
-    launch_infoset_pass(d, rule, counted, st);
+    launch_infoset_pass(d, rule, rule.count != 0, st);
 }
 
 template struct PartDev<float>;

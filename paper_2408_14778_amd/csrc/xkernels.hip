@@ -1075,10 +1075,9 @@ __global__ void k_x_br_reach(int32_t lo, int32_t hi, int64_t N, const int32_t* _
     }
 }
 
-// Every level in one launch: each decision node of lo .. hi - 1 walks up to its root (nodes below
-// n_roots) and multiplies the edges on its path (path_applies says when).
-__global__ void __launch_bounds__(256) k_x_br_reach_path(int32_t lo, int32_t hi, int32_t n_roots,
-                                                         int64_t N,
+// Several levels in one launch: each decision node of lo .. hi - 1 walks up to a node below `stop`, whose
+// reach is stored, and multiplies the edges on its path (walk_groups).
+__global__ void __launch_bounds__(256) k_x_br_reach_path(int32_t lo, int32_t hi, int32_t stop, int64_t N,
                                                          const int32_t* __restrict__ parent,
                                                          const int32_t* __restrict__ edge,
                                                          const int8_t* __restrict__ meta,
@@ -1087,15 +1086,16 @@ __global__ void __launch_bounds__(256) k_x_br_reach_path(int32_t lo, int32_t hi,
     const int64_t x = lo + gid();
     if (x >= hi || (meta[x] & 3) == 0) return;
     float r0 = 1.0f, r1 = 1.0f;
-    for (int32_t y = static_cast<int32_t>(x); y >= n_roots;) {
+    int32_t y = static_cast<int32_t>(x);
+    while (y >= stop) {
         const int actor = meta[y] >> 2;  // 1 chance, 2 player 1, 3 player 2
         const float s = avgprob[edge[y]];
         y = parent[y];
         if (actor != 2) r0 *= s;  // chance or player 2 moved: pi_{-1}
         if (actor != 3) r1 *= s;  // chance or player 1 moved: pi_{-2}
     }
-    br_reach[x] = r0;
-    br_reach[N + x] = r1;
+    br_reach[x] = r0 * br_reach[y];
+    br_reach[N + x] = r1 * br_reach[N + y];
 }
 
 struct BrArgs {
@@ -1662,14 +1662,15 @@ void launch_br_cap(const XDev& x, const BrArgs& a, int32_t l, hipStream_t st) {
 
 void launch_x_best_response(const XDev& x, const float* avgprob, double* out, hipStream_t st) {
     const int32_t* lo = x.level_offset_host;
-    if (x.D > 1 && path_applies(x.N, x.D))
-        hipLaunchKernelGGL(k_x_br_reach_path, dim3(blocks_of(lo[x.D] - lo[1], kBlock)), dim3(kBlock), 0,
-                           st, lo[1], lo[x.D], lo[1], x.N, x.parent, x.edge, x.meta, avgprob,
-                           x.br_reach);
-    else for (int32_t l = 1; l < x.D; ++l)
-        hipLaunchKernelGGL(k_x_br_reach, dim3(blocks_of(lo[l + 1] - lo[l], 2 * kBlock)), dim3(kBlock),
-                           0, st, lo[l], lo[l + 1], x.N, x.parent, x.edge, x.meta, avgprob,
-                           x.br_reach);
+    walk_groups(lo, x.D - 1, [&](int32_t a, int32_t b) {
+        if (b - a > 1)
+            hipLaunchKernelGGL(k_x_br_reach_path, dim3(blocks_for(lo[b] - lo[a])), dim3(kBlock), 0, st,
+                               lo[a], lo[b], lo[a], x.N, x.parent, x.edge, x.meta, avgprob,
+                               x.br_reach);
+        else
+            hipLaunchKernelGGL(k_x_br_reach, dim3(blocks_of(lo[b] - lo[a], 2 * kBlock)), dim3(kBlock), 0,
+                               st, lo[a], lo[b], x.N, x.parent, x.edge, x.meta, avgprob, x.br_reach);
+    });
     BrArgs a;
     a.N = x.N;
     a.chunk_first = x.chunk_first;
