@@ -203,7 +203,14 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
             // subtrees of at most a fraction of a bin: small ones balance, large ones leave a
             // small trunk
             const int64_t even = (N + want - 1) / want;
-            for (int64_t t = std::max<int64_t>(even / 16, 16); t <= even && !found; t *= 2) {
+            // (then sizes between them: 2.58 million nodes fit one bin per workgroup at one of these
+            // only, 58 us per iteration against 70 with two)
+            std::vector<int64_t> sizes;
+            for (const int64_t num : {2, 3})
+                for (int64_t t = std::max<int64_t>(even / 16, 16); t * num / 2 <= even; t *= 2)
+                    sizes.push_back(t * num / 2);
+            for (size_t k = 0; k < sizes.size() && !found; ++k) {
+                const int64_t t = sizes[k];
                 // the trunk, level by level from the root
                 roots.clear();
                 for (int32_t v : in_trunk) trunk[v] = 0;
@@ -236,31 +243,32 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
                     const int32_t ea = edge_of(L.child_begin[a]), eb = edge_of(L.child_begin[b]);
                     return ea != eb ? ea < eb : a < b;
                 });
-                int64_t total = 0, most = 0;
+                int64_t total = 0, most = 0, most_d = td;
                 for (int32_t v : roots) {
                     total += sn[v];
                     most = std::max<int64_t>(most, sn[v]);
+                    most_d = std::max<int64_t>(most_d, sd[v]);
                 }
                 for (int64_t cap = std::max((total + want - 1) / want, most); cap < 2 * total + 2;
                      cap += cap / 32 + 1) {
+                    // every workgroup's arrays have room for `cap` nodes and for the decision nodes that
+                    // LDS holds beside them; a bin ends at either (by nodes alone, 2.58 million nodes
+                    // took two bins per workgroup: where many of them decide the bins overflowed)
+                    const int64_t cap_n = std::max(cap, tn);
+                    const int64_t cap_d = std::min<int64_t>(
+                        65535, (kResLds - bin_bytes(cap_n, 0)) / bin_bytes(0, 1));
+                    if (cap_n > 65535 || bin_bytes(cap_n, most_d) > kResLds) break;
                     bin_root.assign(1, 0);
-                    // (every workgroup's arrays have room for the largest bin's nodes and ranks)
-                    int64_t n = 0, d = 0, most_n = tn, most_d = td;
-                    bool fits = true;
+                    int64_t n = 0, d = 0;
                     for (size_t i = 0; i < roots.size(); ++i) {
                         const int32_t v = roots[i];
-                        if (i == 0 || n + sn[v] > cap) {
+                        if (i == 0 || n + sn[v] > cap || d + sd[v] > cap_d) {
                             bin_root.push_back(static_cast<int32_t>(i));
                             n = d = 0;
                         }
                         n += sn[v];
                         d += sd[v];
-                        most_n = std::max(most_n, n);
-                        most_d = std::max(most_d, d);
-                        fits = most_n <= 65535 && most_d <= 65535 && bin_bytes(most_n, most_d) <= kResLds;
-                        if (!fits) break;
                     }
-                    if (!fits) break;  // larger bins fit less
                     if (static_cast<int64_t>(bin_root.size()) - 1 <= want) {
                         found = true;
                         P.mode = RES_TEAM;
