@@ -11,17 +11,13 @@
 #include <algorithm>
 
 #include "kernels.hpp"
+#include "sum_order.hpp"
 
 namespace cfr {
 
 namespace {
 
 constexpr int kBlock = 256;
-// Levels of at most this many nodes run the general-sum values one wavefront per node, and of at
-// most kWideTop nodes (a root dealing many private types, the levels just below it) a
-// workgroup of 1024 per node.
-constexpr int32_t kWideNodes = 4096;
-constexpr int32_t kWideTop = 16;
 
 inline unsigned blocks_for(int64_t n) {
     return static_cast<unsigned>((n + kBlock - 1) / kBlock);
@@ -809,14 +805,12 @@ void launch_gather_w(const DevT<F>& d, hipStream_t st) {
                            d.infoset_player, d.reach, d.contrib, d.rtilde, d.pibar);
 }
 
-// The wavefronts per infoset follow the mean member count (one pass of the workgroup over the
-// members of an average infoset, at most four wavefronts).
 template <class F>
 void launch_gather(const DevT<F>& d, hipStream_t st) {
     if (d.contrib == nullptr || d.Hp <= 0) return;
-    const int64_t mean = (d.M + d.Hp - 1) / d.Hp;
-    if (mean <= 64) launch_gather_w<F, 1>(d, st);
-    else if (mean <= 128) launch_gather_w<F, 2>(d, st);
+    const int32_t waves = gather_waves(d.M, d.Hp);
+    if (waves == 1) launch_gather_w<F, 1>(d, st);
+    else if (waves == 2) launch_gather_w<F, 2>(d, st);
     else launch_gather_w<F, 4>(d, st);
 }
 
@@ -876,8 +870,8 @@ template <class F>
 static void launch_value_range(const DevT<F>& d, int32_t lo, int32_t hi, hipStream_t st) {
     if (hi <= lo) return;
     if (d.players > 0 && hi - lo <= kWideTop)
-        hipLaunchKernelGGL((k_value_wide_n<F, 16>), dim3(static_cast<unsigned>(hi - lo)), dim3(1024),
-                           0, st, lo, hi, d.N, d.players, d.child_begin, d.node_player,
+        hipLaunchKernelGGL((k_value_wide_n<F, kWideWaves>), dim3(static_cast<unsigned>(hi - lo)),
+                           dim3(64 * kWideWaves), 0, st, lo, hi, d.N, d.players, d.child_begin, d.node_player,
                            d.node_edge, d.prob, d.node_slot, d.value, d.reach, d.contrib);
     else if (d.players > 0 && hi - lo <= kWideNodes)
         hipLaunchKernelGGL((k_value_wide_n<F, 1>), dim3(static_cast<unsigned>((hi - lo + 3) / 4)),

@@ -26,14 +26,15 @@
 // of a barrier is resident and every wait ends, whatever else the GPU runs; workgroups that come
 // late leave at once, and a smaller team takes its bins in turn.
 //
-// Sums are formed in the order of the public-block engine's level-by-level launches (values by
-// action, chance nodes by lane groups and a butterfly, infosets by member), so that the two agree
-// bit for bit (two-player games).
+// Sums are formed in the order of the level-by-level launches, so that the two agree bit for bit: the
+// public-block engine's for two players (values by action, chance nodes by lane groups and a
+// butterfly, infosets by member), the node engine's for general sums (sum_order.hpp).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 
 #include "resident.hpp"
+#include "sum_order.hpp"
 
 namespace cfr {
 
@@ -133,9 +134,10 @@ __global__ void __launch_bounds__(kResMaxThreads) k_resident(Resident<F> r, Upda
 #pragma clang fp contract(off)
     constexpr bool SOLO = MODE == RES_SOLO;
     constexpr int CM = NP > 0 ? NP : 1, RM = NP > 0 ? NP : 2;  // at most so many columns, planes
+    constexpr int kLaneUnroll = NP > 0 ? 1 : 4;  // (several columns' reads ahead spill)
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
     __shared__ Rec4 s_tab[kResMaxDepth + 3];
-    __shared__ F s_red[kResMaxThreads / 64][CM];
+    __shared__ F s_red[NP > 0 ? kWideWaves : 1][NP > 0 ? NP : 1];
     __shared__ int s_place;
     __shared__ uint32_t s_size;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -323,8 +325,10 @@ __global__ void __launch_bounds__(kResMaxThreads) k_resident(Resident<F> r, Upda
         const bool downward = wave & 1;
         const int32_t step = nw / 2 * 64, base = (wave >> 1) * 64, at = base + lane;
         for (int i = 0; i < nl; ++i) {
-            const int l = l0 + nl - 1 - i, g = s_tab[l].z;
-            const int32_t r1 = rlo(l + 1), rch = r1 - s_tab[l].w;  // chance nodes from rch
+            const int l = l0 + nl - 1 - i, sums = s_tab[l].z, g = sums & kResLanes;
+            // nodes that share lanes from rch: chance nodes (general sums: in small levels)
+            const int32_t r1 = rlo(l + 1);
+            const int32_t rch = NP > 0 && !(sums & kResGrouped) ? r1 : r1 - s_tab[l].w;
             if (downward) {
                 const int ld = l0 + 1 + i;
                 const int32_t end = i + 1 < nl ? rlo(ld + 1) : 0;
@@ -348,41 +352,78 @@ __global__ void __launch_bounds__(kResMaxThreads) k_resident(Resident<F> r, Upda
                     const int32_t k = static_cast<int32_t>(static_cast<uint32_t>(q.y) >> 20);
                     const int32_t c0 = q.x & 0xFFFF;
                     const F* const s = SOLO ? prob + (rec4[x].y & 0x0FFFFFFF) : sig + c0;
-                    F v[CM];
-#pragma unroll
-                    for (int c = 0; c < CM; ++c) v[c] = F(0);
+                    F* const own = val + (static_cast<uint32_t>(q.x) >> 16);
+                    const F* const w = val + c0;
+                    if constexpr (NP == 0) {
+                        F v = F(0);
 #pragma unroll 4
-                    for (int32_t a = 0; a < k; ++a)
+                        for (int32_t a = 0; a < k; ++a) v = fma_(s[a], w[a], v);
+                        *own = v;
+                    } else {
+                        // a column at a time (all at once spill), its first four children, as good as
+                        // always all, together
+                        F s4[4];
 #pragma unroll
-                        for (int c = 0; c < CM; ++c)
-                            if (c < P) v[c] = fma_(s[a], val[c * mn + c0 + a], v[c]);
+                        for (int a = 0; a < 4; ++a) s4[a] = s[min(a, k - 1)];
+                        for (int32_t c = 0; c < P; ++c) {
+                            const F* const wc = w + c * mn;
+                            F ch[4];
 #pragma unroll
-                    for (int c = 0; c < CM; ++c)
-                        if (c < P) val[c * mn + (static_cast<uint32_t>(q.x) >> 16)] = v[c];
+                            for (int a = 0; a < 4; ++a) ch[a] = wc[min(a, k - 1)];
+                            F v = F(0);
+                            if (!(sums & kResGrouped)) {
+#pragma unroll
+                                for (int a = 0; a < 4; ++a)
+                                    if (a < k) v = fma_(s4[a], ch[a], v);
+#pragma unroll 4
+                                for (int32_t a = 4; a < k; ++a) v = fma_(s[a], wc[a], v);
+                            } else {
+                                // the butterfly over 64 lanes with a child each (at most 16 have one)
+#pragma unroll
+                                for (int a = 0; a < 4; ++a) ch[a] = a < k ? s4[a] * ch[a] : F(0);
+                                F odd = ch[1] + ch[3];
+                                v = ch[0] + ch[2];
+                                if (k > 4) {
+                                    auto at = [&](int32_t i) { return i < k ? s[i] * wc[i] : F(0); };
+                                    v = odd = F(0);
+#pragma unroll 1
+                                    for (int a = 0; a < 4; ++a) {
+                                        const F p = (at(a) + at(a + 8)) + (at(a + 4) + at(a + 12));
+                                        if (a & 1) odd += p;
+                                        else v += p;
+                                    }
+                                }
+                                v += odd;
+                            }
+                            own[c * mn] = v;
+                        }
+                    }
                 }
-                if (g != kResWide && r1 > rch) {
-                    // a chance node by a lane group, then a butterfly
+                if (r1 > rch) {
+                    // a node by a lane group, then a butterfly
                     const int32_t items = (r1 - rch) << g;
                     for (int32_t bs = base; bs < items; bs += step) {
-                        const bool ok = bs + lane < items;
+                        bool ok = bs + lane < items;
                         const int32_t x = rch + ((bs + lane) >> g);
                         const int2 q = ok ? structure(x) : make_int2(0, 0);
                         const int32_t k = static_cast<int32_t>(static_cast<uint32_t>(q.y) >> 20);
+                        if (NP > 0 && (sums & kResWide) && k > 64) ok = false;  // (below)
                         const int32_t c0 = q.x & 0xFFFF;
                         const F* s = sig + c0;
                         if constexpr (SOLO) s = prob + (ok ? rec4[x].y & 0x0FFFFFFF : 0);
+                        // (every column's butterfly step together: one waits for the one before)
                         F v[CM];
 #pragma unroll
                         for (int c = 0; c < CM; ++c) v[c] = F(0);
-                        for (int32_t a = lane & ((1 << g) - 1); a < k; a += 1 << g)
+#pragma unroll kLaneUnroll
+                        for (int32_t a = lane & ((1 << g) - 1); a < (ok ? k : 0); a += 1 << g)
 #pragma unroll
                             for (int c = 0; c < CM; ++c)
                                 if (c < P) v[c] = fma_(s[a], val[c * mn + c0 + a], v[c]);
+                        for (int off = (1 << g) >> 1; off > 0; off >>= 1)
 #pragma unroll
-                        for (int c = 0; c < CM; ++c)
-                            if (c < P)
-                                for (int off = (1 << g) >> 1; off > 0; off >>= 1)
-                                    v[c] += __shfl_xor(v[c], off, 64);
+                            for (int c = 0; c < CM; ++c)
+                                if (c < P) v[c] += __shfl_xor(v[c], off, 64);
                         if (ok && (lane & ((1 << g) - 1)) == 0) {
 #pragma unroll
                             for (int c = 0; c < CM; ++c)
@@ -391,31 +432,27 @@ __global__ void __launch_bounds__(kResMaxThreads) k_resident(Resident<F> r, Upda
                     }
                 }
             }
-            if (g == kResWide) {
-                // a chance node per workgroup: thread t takes children t, t + threads, ...; then
-                // the wavefronts' sums in order
+            if (NP > 0 && (sums & kResWide)) {
+                // its nodes of more than 64 children by the workgroup: wavefront w of kWideWaves takes
+                // children 64 w + lane, then every 64 kWideWaves-th; the wavefronts' sums in order
                 for (int32_t x = rch; x < r1; ++x) {
                     const int2 q = structure(x);
                     const int32_t k = static_cast<int32_t>(static_cast<uint32_t>(q.y) >> 20);
+                    if (k <= 64) continue;
                     const int32_t c0 = q.x & 0xFFFF;
                     const F* const s = SOLO ? prob + (rec4[x].y & 0x0FFFFFFF) : sig + c0;
-                    F v[CM];
-#pragma unroll
-                    for (int c = 0; c < CM; ++c) v[c] = F(0);
-                    for (int32_t a = tid; a < k; a += nt)
-#pragma unroll
-                        for (int c = 0; c < CM; ++c)
-                            if (c < P) v[c] = fma_(s[a], val[c * mn + c0 + a], v[c]);
-#pragma unroll
-                    for (int c = 0; c < CM; ++c)
-                        if (c < P) {
-                            for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_xor(v[c], off, 64);
-                            if (lane == 0) s_red[wave][c] = v[c];
+                    for (int w = wave; w < kWideWaves; w += nw)
+                        for (int32_t c = 0; c < P; ++c) {
+                            F v = F(0);
+                            for (int32_t a = 64 * w + lane; a < k; a += 64 * kWideWaves)
+                                v = fma_(s[a], val[c * mn + c0 + a], v);
+                            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+                            if (lane == 0) s_red[w][c] = v;
                         }
                     __syncthreads();
                     if (tid < P) {
                         F sum = F(0);
-                        for (int w = 0; w < nw; ++w) sum += s_red[w][tid];
+                        for (int w = 0; w < kWideWaves; ++w) sum += s_red[w][tid];
                         val[tid * mn + (static_cast<uint32_t>(q.x) >> 16)] = sum;
                     }
                     __syncthreads();
@@ -527,31 +564,118 @@ __global__ void __launch_bounds__(kResMaxThreads) k_resident(Resident<F> r, Upda
                 }
                 // members four (times the lanes over members) at a time, their reads together. Two
                 // players: added in member order. General sums, whose infosets can hold hundreds of
-                // members: a sum per lane over members, then a butterfly over the lanes
+                // members: in the order of r.waves wavefronts (sum_order.hpp)
                 F racc = F(0), own = F(0);
                 const int32_t stride = res_stride(k, sizeof(F));
                 const int32_t members = act ? s.z : 0;
-                if (NP > 0 || mlog == 0) {
-                    for (int32_t m = ms; m < members; m += 4 << mlog) {
+                if constexpr (NP > 0) {
+                    // lane t of a wavefront's 64 has the members t, t + 64 waves, ...: this one stands
+                    // for the lanes ms + (q << mlog), whose sums meet as in the wavefront's
+                    // butterfly (q in bit-reversed order: the far halves first), then over its own
+                    // neighbours. Lanes and wavefronts past every infoset's members add nothing and
+                    // are left out; four are read together.
+                    auto read = [&](int32_t m, int32_t column) {
+                        const F x = get<SOLO>(&con[s.y + max(min(m, members - 1), 0) * stride + column]);
+                        return m < members ? x : F(0);
+                    };
+                    if (!__any(members > min(64, 4 << mlog))) {
+                        constexpr int kQ[4] = {0, 2, 1, 3};
                         F xr[4], xo[4];
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const F* from = con + s.y + min(m + (i << mlog), members - 1) * stride;
+                            xr[i] = read(ms + (kQ[i] << mlog), j);
+                            xo[i] = read(ms + (kQ[i] << mlog), k);
+                        }
+                        racc = (xr[0] + xr[1]) + (xr[2] + xr[3]);
+                        own = (xo[0] + xo[1]) + (xo[2] + xo[3]);
+                        for (int off = 1 << hlog >> 1; off >= 1 << alog; off >>= 1) {
+                            racc += __shfl_xor(racc, off, 64);
+                            own += __shfl_xor(own, off, 64);
+                        }
+                    } else {
+                        int lq = 0, wu = 1;  // log2 of the q's, wavefronts
+                        while (lq < 6 - mlog && __any(members > 1 << (lq + mlog))) ++lq;
+                        while (wu < r.waves && __any(members > 64 * wu)) ++wu;
+                        // contributions and own reaches together, in double precision one after
+                        // the other (together they spill)
+                        constexpr int U = sizeof(F) == 4 ? 2 : 1;
+                        for (int t = 0; t < 2; t += U) {
+                            F total[U], half[4][U];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) total[u] = F(0);
+                            for (int b = 0; b < wu << lq; b += 4) {
+                                F x[4][U];
+                                int32_t m[4];
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    const int q =
+                                        static_cast<int>(__brev((b + i) & ((1 << lq) - 1)) >> 1 >> (31 - lq));
+                                    m[i] = b + i < wu << lq ? 64 * ((b + i) >> lq) + ms + (q << mlog) : members;
+#pragma unroll
+                                    for (int u = 0; u < U; ++u) x[i][u] = read(m[i], t + u == 0 ? j : k);
+                                }
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    for (int32_t mm = m[i] + 64 * r.waves; mm < members; mm += 64 * r.waves)
+#pragma unroll
+                                        for (int u = 0; u < U; ++u) x[i][u] += read(mm, t + u == 0 ? j : k);
+                                int parts = min(4 >> lq, wu - (b >> lq));  // complete but for their lanes
+                                if (lq >= 1) {
+#pragma unroll
+                                    for (int u = 0; u < U; ++u) {
+                                        x[0][u] += x[1][u];
+                                        x[1][u] = x[2][u] + x[3][u];
+                                        if (lq >= 2) x[0][u] += x[1][u];
+                                    }
+                                }
+                                if (lq >= 2) {
+                                    parts = 1;
+#pragma unroll
+                                    for (int i = 0; i < 4; ++i)
+                                        if (parts != 0 && i < lq - 2) {  // a complete half joins its other half
+                                            const bool second = (b >> (2 + i)) & 1;
+#pragma unroll
+                                            for (int u = 0; u < U; ++u) {
+                                                if (second) x[0][u] = half[i][u] + x[0][u];
+                                                else half[i][u] = x[0][u];
+                                            }
+                                            if (!second) parts = 0;
+                                        }
+                                }
+                                if (parts > 0)
+                                    for (int off = 1 << hlog >> 1; off >= 1 << alog; off >>= 1)
+#pragma unroll
+                                        for (int i = 0; i < 4; ++i)
+                                            if (i < parts)
+#pragma unroll
+                                                for (int u = 0; u < U; ++u)
+                                                    x[i][u] += __shfl_xor(x[i][u], off, 64);
+#pragma unroll
+                                for (int i = 0; i < 4; ++i)
+                                    if (i < parts)
+#pragma unroll
+                                        for (int u = 0; u < U; ++u) total[u] += x[i][u];
+                            }
+                            if (t == 0) racc = total[0];
+                            if (t == 1 || U == 2) own = total[U - 1];
+                        }
+                    }
+                } else if (mlog == 0) {
+                    for (int32_t m = 0; m < members; m += 4) {
+                        F xr[4], xo[4];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const F* from = con + s.y + min(m + i, members - 1) * stride;
                             xr[i] = get<SOLO>(&from[j]);
                             xo[i] = get<SOLO>(&from[k]);
                         }
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            if (m + (i << mlog) < members) {
+                            if (m + i < members) {
                                 racc += xr[i];
                                 own += xo[i];
                             }
                     }
-                    if constexpr (NP > 0)
-                        for (int off = 1 << alog; off < 1 << hlog; off <<= 1) {
-                            racc += __shfl_xor(racc, off, 64);
-                            own += __shfl_xor(own, off, 64);
-                        }
                 } else {
                     for (int32_t m = 0; __any(m < members); m += 4 << mlog) {
                         F xr[4], xo[4];
@@ -647,6 +771,7 @@ void resident_shape(Resident<F>& r, const ResPlan& p) {
     r.mlog = 0;
     const int32_t each = r.players > 0 ? 4 : 16;  // members of a lane
     while (r.alog + r.mlog < 6 && (each << r.mlog) < p.mean_members) ++r.mlog;
+    r.waves = p.waves;
     // a solo game's threads follow its widest work (fewer wavefronts meet sooner)
     int32_t threads = kResMaxThreads;
     if (r.mode == RES_SOLO) {
@@ -676,8 +801,9 @@ void launch_resident(const Resident<F>& r, const UpdateRule& rule, bool alternat
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(r.threads), lds, st, r, rule, passes, m);
         };
         if (r.players > 0) {
-            if (r.mode == RES_SOLO) go(k_resident<F, RES_SOLO, kMaxPlayers>);
-            else go(k_resident<F, RES_TEAM, kMaxPlayers>);
+            const bool few = r.players <= 4;
+            if (r.mode == RES_SOLO) few ? go(k_resident<F, RES_SOLO, 4>) : go(k_resident<F, RES_SOLO, kMaxPlayers>);
+            else few ? go(k_resident<F, RES_TEAM, 4>) : go(k_resident<F, RES_TEAM, kMaxPlayers>);
         } else {
             if (r.mode == RES_SOLO) go(k_resident<F, RES_SOLO, 0>);
             else go(k_resident<F, RES_TEAM, 0>);

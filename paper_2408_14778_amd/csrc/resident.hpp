@@ -39,6 +39,7 @@ struct Resident {
     int64_t n_con = 0;
     int32_t alog = 0;      // log2 of the lanes per infoset: over its actions
     int32_t mlog = 0;      // and over its members
+    int32_t waves = 1;     // general sums: wavefronts whose order the members' sums follow
     int32_t threads = 0;   // threads per workgroup
     Rec4* rec = nullptr;
     int32_t* slot = nullptr;

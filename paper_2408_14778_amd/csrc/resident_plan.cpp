@@ -6,6 +6,8 @@
 #include <functional>
 #include <thread>
 
+#include "sum_order.hpp"
+
 namespace cfr {
 
 namespace {
@@ -291,15 +293,18 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
     P.path.assign(static_cast<size_t>(P.roots) * P.path_len, 0);
     std::vector<int32_t> glog(D + 1, 0);
     for (int32_t l = 0; l < D; ++l) {
-        // lanes per node: the level's largest chance fan-out rounded up to a power of two, at
-        // most a wavefront; a workgroup per node past 256
+        // lanes per chance node: the level's largest fan-out rounded up to a power of two, at most a
+        // wavefront
+        const int32_t nodes = L.level_offset[l + 1] - L.level_offset[l];
+        const bool grouped = z.players > 0 && nodes <= kWideNodes;
         int32_t kmax = 1;
         for (int32_t v = L.level_offset[l]; v < L.level_offset[l + 1]; ++v)
             if (L.node_player[v] == 0)
                 kmax = std::max(kmax, L.child_begin[v + 1] - L.child_begin[v]);
         int32_t g = 0;
         while (g < 6 && (1 << g) < kmax) ++g;
-        glog[l] = kmax > 256 ? kResWide : g;
+        const bool wide = grouped && nodes <= kWideTop && kmax > 64;
+        glog[l] = g | (grouped ? kResGrouped : 0) | (wide ? kResWide : 0);
     }
     std::vector<double> rc;
     std::vector<int32_t> slot, lnode, lrank;
@@ -349,6 +354,7 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
             at += static_cast<int64_t>(n) * res_stride(k, z.real_bytes);
         }
         P.mean_members = L.Hp > 0 ? static_cast<int32_t>(L.n_members / L.Hp) : 0;
+        P.waves = gather_waves(L.n_members, L.Hp);
     };
     if (!run_all(N, {[&] { P.rec.resize(nd); }, [&] { P.slot.assign(nd, 0); },
                      [&] { P.reach_c.resize(nd); },

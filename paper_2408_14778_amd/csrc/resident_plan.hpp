@@ -36,7 +36,12 @@ constexpr int32_t kResTrunk = 32768;    // subtrees
 constexpr int32_t kResPath = 24;        // levels above them
 constexpr int32_t kResXcd = 32;         // CUs of one XCD
 constexpr int64_t kResLds = 150 * 1024; // bytes of a bin's arrays (160 KB less the kernel's own)
-constexpr int32_t kResWide = 10;        // glog of a level whose chance nodes take a workgroup each
+// What a level's entry of ResPlan::table holds in its third word: log2 of the lanes that share a
+// node's children, and how a general-sum game's level sums (sum_order.hpp; a two-player game's
+// chance nodes always sum over their lanes and a butterfly, as the public-block engine's do)
+constexpr int32_t kResLanes = 0xFF;
+constexpr int32_t kResGrouped = 1 << 8;  // over 64 lanes (at most kWideNodes nodes), else in child order
+constexpr int32_t kResWide = 1 << 9;     // at most kWideTop nodes, one with children for a second wavefront
 enum ResMode { RES_SOLO = 0, RES_TEAM = 1 };
 
 // A member's contributions and own reach, padded to 16 bytes.
@@ -100,12 +105,13 @@ struct ResPlan {
     // x, actor 0 past its end)
     std::vector<int32_t> root_rank, ext, path;
     // per bin from table[bin * (depth + 3)], per level of the game: {first local node, first local
-    // rank, glog, chance nodes}; then {rank base in rec, nodes, ranks, node base in node} and
+    // rank, lanes and order of the sums (kRes...), chance nodes}; then {rank base in rec, nodes, ranks, node base in node} and
     // {first level, levels with decision nodes, first root, end of roots}
     std::vector<Rec4> table;
     int32_t max_nodes = 0, max_ranks = 0;  // of a bin
     int64_t contributions = 0;
     int32_t max_actions = 1, mean_members = 0;
+    int32_t waves = 1;  // general sums: gather_waves of the infosets
 };
 
 // A batch as one game: a chance node above the games' roots deals each of them with probability 1, on
