@@ -192,8 +192,10 @@ typedef struct cfr_launch_shape {
 /* Fills `out` with the library's default shapes. */
 void cfr_default_launch_shape(cfr_launch_shape* out);
 
-/* Sets the launch shapes (NULL: the defaults) and re-captures the iteration graph.
- * CFR_EINVAL for a value outside the ranges above, or for the node engine. */
+/* Sets the launch shapes (NULL: the defaults) and re-captures the iteration graph. A solver whose
+ * iterations are one launch (cfr_iterate) runs the level-by-level launches from then on, in the
+ * shapes asked for; NULL returns it to the one launch. CFR_EINVAL for a value outside the ranges
+ * above, or for the node engine. */
 int cfr_set_launch_shape(cfr_solver* s, const cfr_launch_shape* shape);
 
 /* Average strategy sigma-bar = S / sum_a S per infoset, uniform where that sum is 0
@@ -232,9 +234,12 @@ int cfr_set_state_f64(cfr_solver* s, int64_t T, const double* R, const double* S
  * iteration computes the level's reach (0: none, the roots and levels without decision nodes;
  * 1: the single-workgroup launch of the first levels; 2: the launch that walks several small
  * levels up to the last stored one; 3: a launch of its own; 4: the
- * level's bottom-up launch, from the parents' reach; for a batch, the levels of its forest).
+ * level's bottom-up launch, from the parents' reach; for a batch, the levels of its forest), where
+ * iterations run level by level (timed ones always do); or one_launch: four int32, all 0 where
+ * cfr_iterate runs level by level, else 1, the workgroups of the launch, the bins of subtrees that
+ * they take and the most iterations of one launch.
  * cfr_layout_bytes returns the size (< 0 for an unknown name, or for a batch any name but
- * reach_launch). */
+ * reach_launch and one_launch). */
 int64_t cfr_layout_bytes(cfr_solver* s, const char* name);
 int cfr_get_layout(cfr_solver* s, const char* name, void* out, int64_t bytes);
 

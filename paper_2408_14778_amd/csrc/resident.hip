@@ -791,12 +791,12 @@ template <class F>
 void launch_resident(const Resident<F>& r, const UpdateRule& rule, bool alternating, int32_t n,
                      hipStream_t st) {
     const int32_t passes = alternating ? (r.players > 0 ? r.players : 2) : 1;
-    constexpr int32_t kMost = 1 << 14;  // iterations of one launch
+    const int32_t most = resident_launch_iterations(r);
     const size_t lds = lds_bytes(r);
     // workgroups go to the XCDs in turn: eight per member of a one-XCD team bring them to each
     const int32_t grid = r.mode == RES_SOLO ? 1 : r.team_size <= kResXcd ? 8 * r.team_size : r.team_size;
-    for (int32_t i = 0; i < n; i += kMost) {
-        const int32_t m = std::min(kMost, n - i);
+    for (int32_t i = 0; i < n; i += most) {
+        const int32_t m = std::min(most, n - i);
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(r.threads), lds, st, r, rule, passes, m);
         };

@@ -67,6 +67,12 @@ void resident_shape(Resident<F>& r, const ResPlan& p);
 // Clears the team, once, when the solver is set up.
 template <class F>
 void launch_resident_reset(const Resident<F>& r, hipStream_t st);
+// The most iterations of one launch.
+constexpr int32_t kResIterations = 1 << 14;
+template <class F>
+int32_t resident_launch_iterations(const Resident<F>&) {
+    return kResIterations;
+}
 // n iterations (alternating: a pass per player each), T += n.
 template <class F>
 void launch_resident(const Resident<F>& r, const UpdateRule& rule, bool alternating, int32_t n,

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <atomic>
 #include <future>
 #include <memory>
@@ -46,7 +47,9 @@ struct cfr_solver {
     // small game: whole iterations in one launch (the one of the solver's precision is set up)
     cfr::Resident<float> res32;
     cfr::Resident<double> res64;
-    bool resident = false;
+    bool resident = false;      // its records are on the device
+    bool shaped = false;        // launch shapes were asked for: its iterations are launches of them
+    bool one_launch() const { return resident && !shaped; }  // what cfr_iterate does
     std::vector<int32_t> res_node, res_rank_node;  // canonical node of its nodes, decision nodes
     bool resident_values = false;  // the last iteration's node values and reach are the resident ones
     cfr::XDev xdev{};
@@ -1267,7 +1270,7 @@ int cfr_build_partitioned(const cfr_game* game, const cfr_config* config, int32_
 
 int cfr_iterate(cfr_solver* s, int32_t n) {
     if (s == nullptr || n < 0) return set_err(CFR_EINVAL, "bad solver or count");
-    if (s->resident && n > 0) {
+    if (s->one_launch() && n > 0) {
         if (s->fp64) cfr::launch_resident(s->res64, s->rule, s->alternating, n, s->stream);
         else cfr::launch_resident(s->res32, s->rule, s->alternating, n, s->stream);
         if (const int rc = check_hip("iteration launch"); rc != CFR_OK) return rc;
@@ -1275,6 +1278,7 @@ int cfr_iterate(cfr_solver* s, int32_t n) {
         s->T += n;
         return CFR_OK;
     }
+    if (n > 0) s->resident_values = false;
     for (int32_t i = 0; i < n; ++i) {
         if (s->use_graph) {
             HIP_TRY(hipGraphLaunch(s->exec, s->stream), "graph launch");
@@ -1433,7 +1437,8 @@ int cfr_set_launch_shape(cfr_solver* s, const cfr_launch_shape* shape) {
     if (s->graph != nullptr) (void)hipGraphDestroy(s->graph);
     s->exec = nullptr;
     s->graph = nullptr;
-    if (s->use_graph && !s->resident) return capture(s);
+    s->shaped = shape != nullptr;
+    if (s->use_graph && !s->one_launch()) return capture(s);
     return CFR_OK;
 }
 
@@ -1607,6 +1612,7 @@ int cfr_set_state_f64(cfr_solver* s, int64_t T, const double* R, const double* S
 int64_t cfr_layout_bytes(cfr_solver* s, const char* name) {
     if (s == nullptr || name == nullptr) return CFR_EINVAL;
     const std::string n(name);
+    if (n == "one_launch") return 4 * 4;
     if (s->partitioned()) return CFR_EINVAL;  // no canonical arrays on the device
     if (n == "reach_launch") return (launch_depth(s) + 1) * 4;  // batches too
     if (!s->canonical) return CFR_EINVAL;
@@ -1636,6 +1642,16 @@ int cfr_get_layout(cfr_solver* s, const char* name, void* out, int64_t bytes) {
     const std::string n(name);
     if (n == "reach_launch") {
         const std::vector<int32_t> r = reach_launch(s);
+        std::memcpy(out, r.data(), bytes);
+        return CFR_OK;
+    }
+    if (n == "one_launch") {
+        const auto shape = [](const auto& r) {
+            return std::array<int32_t, 4>{1, r.mode == cfr::RES_SOLO ? 1 : r.team_size, r.bins,
+                                          cfr::resident_launch_iterations(r)};
+        };
+        std::array<int32_t, 4> r{};
+        if (s->one_launch()) r = s->fp64 ? shape(s->res64) : shape(s->res32);
         std::memcpy(out, r.data(), bytes);
         return CFR_OK;
     }

@@ -24,7 +24,7 @@ LAYOUT_DTYPES = {
     "members": np.int32, "chance_prob": np.float32, "payoff": np.float32, "q_input": np.int32,
 }
 # per-solver launch facts exported by the same call (not part of the canonical layout)
-SOLVER_LAYOUT_DTYPES = {"reach_launch": np.int32}
+SOLVER_LAYOUT_DTYPES = {"reach_launch": np.int32, "one_launch": np.int32}
 
 
 def _ptr(a: np.ndarray, ctype):
@@ -214,7 +214,7 @@ class Solver:
         self._f64 = precision == "f64"
         self._rdt = np.float64 if self._f64 else np.float32
         self._sfx = "_f64" if self._f64 else ""
-        if tuned and not self._f64:
+        if tuned and not self._f64 and not self.one_launch:
             from . import autotune
             autotune.apply(self, autotune.load())
 
@@ -255,7 +255,8 @@ class Solver:
         """Launch shapes per log2 bucket of work items: bottom-up threads per workgroup and
         members per thread, top-down threads per workgroup and nodes per thread (a scalar or
         a list of up to 32 buckets, the last entry repeated). Arguments left None keep the
-        library default; all None restores every default."""
+        library default; all None restores every default. A solver whose iterations are one
+        launch (one_launch) runs level by level in the shapes asked for until then."""
         if all(v is None for v in (up_threads, reach_threads, up_members, reach_nodes)):
             N.check(self._lib.cfr_set_launch_shape(self._h, None))
             return
@@ -268,6 +269,12 @@ class Solver:
             vals = (vals + [vals[-1]] * 32)[:32]
             getattr(sh, name)[:] = vals
         N.check(self._lib.cfr_set_launch_shape(self._h, ctypes.byref(sh)))
+
+    @property
+    def one_launch(self) -> bool:
+        """Whether iterate() runs whole iterations in one launch (small and middle-sized games;
+        layout("one_launch") gives its workgroups, bins and most iterations)."""
+        return bool(self.layout("one_launch")[0])
 
     def synchronize(self) -> None:
         self.stream.synchronize()
@@ -515,7 +522,7 @@ class BatchSolver(Solver):
         self.n_nodes = int(info.n_nodes)
         qs = [int(np.sum(g.infoset_num_actions[g.infoset_player != 0])) for g in game_list]
         self.pair_offsets = np.concatenate([[0], np.cumsum(qs)]).astype(np.int64)
-        if tuned:
+        if tuned and not self.one_launch:
             from . import autotune
             autotune.apply(self, autotune.load())
 
