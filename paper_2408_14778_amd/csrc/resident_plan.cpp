@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <atomic>
 #include <functional>
+#include <new>
 #include <thread>
 
 #include "sum_order.hpp"
@@ -146,8 +147,9 @@ Layout forest_layout(const std::vector<Layout>& games) {
     return L;
 }
 
-bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResSizes& z,
-                    ResPlan& P) {
+namespace {
+
+bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResSizes& z, ResPlan& P) {
     const int64_t N = L.N;
     const int32_t D = L.D;
     const int64_t cols = columns(z), pl = planes(z), real = z.real_bytes;
@@ -356,15 +358,19 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
         P.mean_members = L.Hp > 0 ? static_cast<int32_t>(L.n_members / L.Hp) : 0;
         P.waves = gather_waves(L.n_members, L.Hp);
     };
-    if (!run_all(N, {[&] { P.rec.resize(nd); }, [&] { P.slot.assign(nd, 0); },
-                     [&] { P.reach_c.resize(nd); },
-                     [&] {
-                         P.rank_node.resize(nd);
-                         P.node.resize(N + P.roots);
-                     },
-                     [&] { lnode.assign(N, -1); }, [&] { lrank.assign(N, -1); }, chance_products,
-                     number_sets}))
-        return false;
+    std::vector<std::function<void()>> jobs;
+    jobs.emplace_back([&] { P.rec.resize(nd); });
+    jobs.emplace_back([&] { P.slot.assign(nd, 0); });
+    jobs.emplace_back([&] { P.reach_c.resize(nd); });
+    jobs.emplace_back([&] {
+        P.rank_node.resize(nd);
+        P.node.resize(N + P.roots);
+    });
+    jobs.emplace_back([&] { lnode.assign(N, -1); });
+    jobs.emplace_back([&] { lrank.assign(N, -1); });
+    jobs.emplace_back(chance_products);
+    jobs.emplace_back(number_sets);
+    if (!run_all(N, jobs)) return false;
     // where each bin's ranks and nodes begin
     std::vector<int64_t> rbase_of(P.bins, 0), nbase_of(P.bins, 0);
     if (team) {
@@ -486,6 +492,18 @@ bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const Res
         P.max_ranks = std::max(P.max_ranks, bin_ranks[b]);
     }
     return true;
+}
+
+}  // namespace
+
+bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResSizes& z,
+                    ResPlan& P) {
+    try {
+        if (plan_resident(L, q_of, z, P)) return true;
+    } catch (const std::bad_alloc&) {
+    }
+    P = ResPlan{};
+    return false;
 }
 
 }  // namespace cfr

@@ -120,7 +120,8 @@ struct ResPlan {
 Layout forest_layout(const std::vector<Layout>& games);
 
 // Plans layout L; q_of[h]: the first pair of canonical rational infoset h in the engine's order.
-// False: no split whose bins fit (the game stays on the level-by-level launches).
+// False, and an empty plan: no split whose bins fit, or no memory for it (the game stays on the
+// level-by-level launches).
 bool build_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResSizes& z,
                     ResPlan& out);
 

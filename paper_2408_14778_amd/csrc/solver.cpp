@@ -8,6 +8,7 @@
 #include <memory>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <thread>
 #include <type_traits>
 #include <utility>
@@ -915,29 +916,33 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     cfr::ResPlan rp;
     std::vector<float> reach_c32, res_pay32;
     std::vector<double> res_pay64;
+    // payoffs in the bins' order
+    const auto in_bins = [&](const auto& pay, auto& out) {
+        const int64_t nb = static_cast<int64_t>(rp.node.size()), cols = players > 0 ? players : 1;
+        out.resize(cols * nb);
+        for (int64_t c = 0; c < cols; ++c)
+            cfr::for_ranges(nb, [&](int64_t i0, int64_t i1) {
+                for (int64_t i = i0; i < i1; ++i) out[c * nb + i] = pay[c * L.N + rp.node[i]];
+            });
+    };
     const auto plan_records = [&] {
-        std::vector<int32_t> q_of(L.q_offset.begin(), L.q_offset.begin() + L.Hp);
-        if (z.engine == ENGINE_BLOCK)
-            for (int64_t e = 0; e < L.Hp; ++e) q_of[P.infoset_canon[e]] = P.q_offset[e];
-        if (!cfr::build_resident(L, q_of, resident_sizes(z), rp)) return false;
-        if (!fp64) reach_c32.assign(rp.reach_c.begin(), rp.reach_c.end());
-        // payoffs in the bins' order
-        const auto in_bins = [&](const auto& pay, auto& out) {
-            const int64_t nb = static_cast<int64_t>(rp.node.size()), cols = players > 0 ? players : 1;
-            out.resize(cols * nb);
-            for (int64_t c = 0; c < cols; ++c)
-                cfr::for_ranges(nb, [&](int64_t i0, int64_t i1) {
-                    for (int64_t i = i0; i < i1; ++i) out[c * nb + i] = pay[c * L.N + rp.node[i]];
-                });
-        };
-        if (fp64) in_bins(players > 0 ? pay64 : L.payoff64, res_pay64);
-        else in_bins(players > 0 ? pay32 : L.payoff, res_pay32);
-        return true;
+        try {
+            std::vector<int32_t> q_of(L.q_offset.begin(), L.q_offset.begin() + L.Hp);
+            if (z.engine == ENGINE_BLOCK)
+                for (int64_t e = 0; e < L.Hp; ++e) q_of[P.infoset_canon[e]] = P.q_offset[e];
+            if (!cfr::build_resident(L, q_of, resident_sizes(z), rp)) return false;
+            if (!fp64) reach_c32.assign(rp.reach_c.begin(), rp.reach_c.end());
+            if (fp64) in_bins(players > 0 ? pay64 : L.payoff64, res_pay64);
+            else in_bins(players > 0 ? pay32 : L.payoff, res_pay32);
+            return true;
+        } catch (const std::bad_alloc&) {  // (the solver then runs level by level)
+            return false;
+        }
     };
     std::future<bool> records;  // (waits in its destructor)
     if (z.resident) try {
             records = std::async(std::launch::async, plan_records);
-        } catch (const std::system_error&) {  // no thread: planned below
+        } catch (...) {  // no thread: planned below
         }
     const auto plan_resident = [&] { return records.valid() ? records.get() : plan_records(); };
     auto* s = new cfr_solver();
@@ -1987,7 +1992,7 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     cfr::launch_x_reset(s->xdev, st);
     cfr::ResPlan rp;
     std::vector<float> reach_c, pay;
-    if (z.resident) {
+    if (z.resident) try {
         const cfr::Layout L = cfr::forest_layout(layouts);
         // each infoset's pairs in the plan: by the input pair of its first
         std::vector<int32_t> pair_of(F.Qp), q_of(F.Hp);
@@ -2002,9 +2007,11 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
         cfr::for_ranges(static_cast<int64_t>(pay.size()), [&](int64_t i0, int64_t i1) {
             for (int64_t i = i0; i < i1; ++i) pay[i] = L.payoff[rp.node[i]];
         });
+        reach_c.assign(rp.reach_c.begin(), rp.reach_c.end());
+    } catch (const std::bad_alloc&) {  // (the batch then runs level by level)
+        s->resident = false;
     }
     if (s->resident) {
-        reach_c.assign(rp.reach_c.begin(), rp.reach_c.end());
         if ((rc = upload_resident(s->res32, rp, reach_c, pay, st)) != CFR_OK) {
             discard(s);
             return rc;
