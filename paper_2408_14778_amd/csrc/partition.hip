@@ -57,13 +57,14 @@ __device__ __forceinline__ void decode(const Sets& s, int32_t code, int32_t& edg
 }
 
 // The regret contributions and own reach of a player's node with value u, added to the per-pair
-// and per-infoset accumulators (signs and reaches as the node engine's bottom-up pass).
-template <class F>
+// and per-infoset accumulators (signs and reaches as the node engine's bottom-up pass);
+// child_value(a): the value of action a's child.
+template <class F, class V>
 __device__ __forceinline__ void add_node(int who, int32_t h, int32_t edge, int32_t k, F u, F r1, F r2,
-                                         F rc, const F* child_value, F* rtilde, F* pibar) {
+                                         F rc, const V& child_value, F* rtilde, F* pibar) {
     const F cf = (who == 1 ? r2 : r1) * rc;
     const F w = who == 1 ? cf : -cf;
-    for (int32_t a = 0; a < k; ++a) unsafeAtomicAdd(&rtilde[edge + a], w * (child_value[a] - u));
+    for (int32_t a = 0; a < k; ++a) unsafeAtomicAdd(&rtilde[edge + a], w * (child_value(a) - u));
     unsafeAtomicAdd(&pibar[h], who == 1 ? r1 : r2);
 }
 
@@ -110,8 +111,8 @@ __global__ void k_mid_up(int32_t n, int32_t id0, int64_t N, Sets s, const int32_
     for (int32_t a = 0; a < k; ++a) u = fma_(prob[edge + a], value[c0 + a], u);
     value[id] = u;
     if (who > 0)
-        add_node(who, h, edge, k, u, reach[id], reach[N + id], reach[2 * N + id], value + c0, rtilde,
-                 pibar);
+        add_node(who, h, edge, k, u, reach[id], reach[N + id], reach[2 * N + id],
+                 [&](int32_t a) { return value[c0 + a]; }, rtilde, pibar);
 }
 
 // A run of subtrees, one workgroup: every record is read once from host memory and staged with the
@@ -128,15 +129,16 @@ __global__ void __launch_bounds__(kThreads) k_stream_run(const StreamUnit* __res
     constexpr int kPart = kStreamPart, kWaves = kThreads / 64;
     extern __shared__ uint64_t s_mem[];
     __shared__ int32_t s_sum[kWaves];
-    // per node: edge probability, value (a decision's code until then), reaches; first edge; who (2
-    // bits), fan-out (12) and first child (12)
+    // per node: edge probability, value (a decision's code until then: words of one type, so that a
+    // code's read stays ahead of the value's write), reaches; first edge; who (2 bits), fan-out
+    // (12) and first child (12)
     F* const s_prob = reinterpret_cast<F*>(s_mem);
-    F* const s_val = s_prob + cap;
-    F *const s_r1 = s_val + cap, *const s_r2 = s_r1 + cap, *const s_rc = s_r2 + cap;
+    W* const s_word = reinterpret_cast<W*>(s_prob + cap);
+    F *const s_r1 = reinterpret_cast<F*>(s_word + cap), *const s_r2 = s_r1 + cap, *const s_rc = s_r2 + cap;
     int32_t* const s_edge = reinterpret_cast<int32_t*>(s_rc + cap);
     uint32_t* const s_meta = reinterpret_cast<uint32_t*>(s_edge + cap);
     uint16_t* const s_level = reinterpret_cast<uint16_t*>(s_meta + cap);  // cap + 2 level offsets
-    W* const s_word = reinterpret_cast<W*>(s_val);
+    auto value_of = [&](int i) { return __builtin_bit_cast(F, s_word[i]); };
     auto first_child = [&](int i) { return static_cast<int>(s_meta[i] >> 14); };
 
     const int tid = static_cast<int>(threadIdx.x), lane = tid & 63, wave = tid >> 6;
@@ -231,16 +233,17 @@ __global__ void __launch_bounds__(kThreads) k_stream_run(const StreamUnit* __res
             const int who = m & 3, k = (m >> 2) & 0xfff, c = m >> 14;
             if (who == 3) continue;
             F v = F(0);
-            for (int a = c; a < c + k; ++a) v = fma_(s_prob[a], s_val[a], v);
+            for (int a = c; a < c + k; ++a) v = fma_(s_prob[a], value_of(a), v);
             const int32_t h = static_cast<int32_t>(s_word[i]);
-            s_val[i] = v;
+            s_word[i] = __builtin_bit_cast(W, v);
             if (who > 0)
-                add_node(who, h, s_edge[i], k, v, s_r1[i], s_r2[i], s_rc[i], s_val + c, rtilde, pibar);
+                add_node(who, h, s_edge[i], k, v, s_r1[i], s_r2[i], s_rc[i],
+                         [&](int32_t a) { return value_of(c + a); }, rtilde, pibar);
         }
         hi = lo;
         __syncthreads();
     }
-    for (int i = tid; i < roots; i += kThreads) value[u.id0 + i] = s_val[i];
+    for (int i = tid; i < roots; i += kThreads) value[u.id0 + i] = value_of(i);
 }
 
 template <class F>
