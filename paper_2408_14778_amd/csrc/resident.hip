@@ -791,7 +791,7 @@ template <class F>
 void launch_resident(const Resident<F>& r, const UpdateRule& rule, bool alternating, int32_t n,
                      hipStream_t st) {
     const int32_t passes = alternating ? (r.players > 0 ? r.players : 2) : 1;
-    const int32_t most = resident_launch_iterations(r);
+    const int32_t most = resident_launch_iterations(r, passes);
     const size_t lds = lds_bytes(r);
     // workgroups go to the XCDs in turn: eight per member of a one-XCD team bring them to each
     const int32_t grid = r.mode == RES_SOLO ? 1 : r.team_size <= kResXcd ? 8 * r.team_size : r.team_size;

@@ -67,11 +67,14 @@ void resident_shape(Resident<F>& r, const ResPlan& p);
 // Clears the team, once, when the solver is set up.
 template <class F>
 void launch_resident_reset(const Resident<F>& r, hipStream_t st);
-// The most iterations of one launch.
-constexpr int32_t kResIterations = 1 << 14;
+// The most iterations of one launch: about 5 ms of a full team's work. A launch keeps the team that it
+// formed; one that formed while other work held the CUs is slower, and the next launch forms anew. A
+// launch costs 6 to 10 us, so shorter ones would show. An iteration's time is taken as 4 us and 22 ps a
+// node and pass (617 nodes and three passes 3.3 us, 2.6 million nodes 58 us, 5.5 million 124 us).
 template <class F>
-int32_t resident_launch_iterations(const Resident<F>&) {
-    return kResIterations;
+int32_t resident_launch_iterations(const Resident<F>& r, int32_t passes) {
+    const double us = 4.0 + 22e-6 * static_cast<double>(r.N) * passes;
+    return static_cast<int32_t>(5000.0 / us) > 16 ? static_cast<int32_t>(5000.0 / us) : 16;
 }
 // n iterations (alternating: a pass per player each), T += n.
 template <class F>

@@ -1651,9 +1651,10 @@ int cfr_get_layout(cfr_solver* s, const char* name, void* out, int64_t bytes) {
         return CFR_OK;
     }
     if (n == "one_launch") {
-        const auto shape = [](const auto& r) {
+        const int32_t passes = !s->alternating ? 1 : s->players > 0 ? s->players : 2;
+        const auto shape = [&](const auto& r) {
             return std::array<int32_t, 4>{1, r.mode == cfr::RES_SOLO ? 1 : r.team_size, r.bins,
-                                          cfr::resident_launch_iterations(r)};
+                                          cfr::resident_launch_iterations(r, passes)};
         };
         std::array<int32_t, 4> r{};
         if (s->one_launch()) r = s->fp64 ? shape(s->res64) : shape(s->res32);
