@@ -300,9 +300,10 @@ def _timed(solver, steps: int):
 
 
 def bench_nplayer(args, g) -> dict:
-    """A three-player general-sum game (games.random_game_n, NPLAYER_GAME) on the node engine's
-    general-sum kernels (cfr_build_n), CFR+: node-updates/s and the roofline of the dominant
-    kernel under algorithmic_bytes_n."""
+    """A three-player general-sum game (games.random_game_n, NPLAYER_GAME) through cfr_build_n,
+    CFR+: node-updates/s of the solver's own route, and the roofline of the dominant level-by-level
+    kernel under algorithmic_bytes_n. Where iterations are one launch, that kernel's share is of
+    the level-by-level iteration of a second solver (graph=False), never of the one launch's time."""
     from paper_2408_14778_amd import NPlayerSolver
 
     real = 8 if args.precision == "f64" else 4
@@ -311,34 +312,48 @@ def bench_nplayer(args, g) -> dict:
     passes = g.n_players if args.schedule == "alternating" else 1
     s.iterate(args.warmup)
     wall_s, gpu_s = _timed(s, args.steps)
-    kt = s.iterate_timed(args.timed_kernel_steps)
+    one = s.one_launch
+    level, level_s = s, gpu_s
+    if one:
+        level = NPlayerSolver(g, "cfr+", precision=args.precision, schedule=args.schedule,
+                              graph=False)
+        level.iterate(args.warmup)
+        _, level_s = _timed(level, args.steps)
+    kt = level.iterate_timed(args.timed_kernel_steps)
     lay = {k: s.layout(k) for k in LAYOUT_FOR_COUNTS}
     counts = level_counts(lay)
     dom = max(kt, key=lambda k: kt[k][1])
     launches, total_ms = kt[dom]
     share = total_ms / sum(v[1] for v in kt.values())
-    avg_s = gpu_s * share / (launches / args.timed_kernel_steps)
+    avg_s = level_s * share / (launches / args.timed_kernel_steps)
     P = g.n_players
     bytes_per_launch = (algorithmic_bytes_n(dom, counts, P, real) * passes *
                         args.timed_kernel_steps / launches)
     achieved = bytes_per_launch / avg_s / 1e9
     iter_bytes = passes * float(sum(algorithmic_bytes_n(k, counts, P, real)
                                     for k in ("reach_level", "value_level", "infoset_update")))
+    _, workgroups, bins, _ = (int(x) for x in s.layout("one_launch"))
+    if one:
+        level.close()
     s.close()
     return {"metric": METRIC, "value": g.n_nodes * passes / wall_s, "unit": "node-updates/s",
             "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
             "ms_per_step": wall_s * 1e3, "higher_is_better": True, "scaling": "weak",
             "vs_baseline": None, "dtype": args.precision, "data": "synthetic",
             "config": {"workload": "three-player general-sum random game (private types 12 per "
-                                   "player, public depth 9), CFR+, node engine" +
+                                   "player, public depth 9), CFR+, " +
+                                   ("iterations in one launch" if one else "node engine") +
                                    (", alternating updates" if passes > 1 else ""),
                        "game": NPLAYER_GAME, "nodes": g.n_nodes, "q": s.n_q, "players": P,
                        "passes_per_iteration": passes},
+            "one_launch": {"workgroups": workgroups, "bins": bins, "iteration_us_events": gpu_s * 1e6}
+            if one else None,
             "roofline": {"bound": "hbm", "kernel": dom, "achieved": achieved,
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                          "traffic": None, "bytes_per_launch": bytes_per_launch,
-                         "avg_launch_us": avg_s * 1e6, "iteration_us_events": gpu_s * 1e6,
-                         "iteration_bytes": iter_bytes, "iteration_gbs": iter_bytes / gpu_s / 1e9},
+                         "route": "level by level, direct launches" if one else "graph replay",
+                         "avg_launch_us": avg_s * 1e6, "iteration_us_events": level_s * 1e6,
+                         "iteration_bytes": iter_bytes, "iteration_gbs": iter_bytes / level_s / 1e9},
             "kernels": {k: {"launches": n, "avg_us": ms / n * 1e3} for k, (n, ms) in kt.items()}}
 
 
