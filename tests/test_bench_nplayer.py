@@ -44,7 +44,7 @@ def _fake(game, resident):
 
 @pytest.mark.parametrize("resident", [True, False])
 def test_kernel_shares_are_of_the_route_they_ran_on(monkeypatch, resident):
-    g = games.normal_form_n(np.arange(24.0).reshape(2, 3, 2, 2) / 64)
+    g = games.normal_form_n(np.arange(36.0).reshape(2, 3, 2, 3) / 64)
     fake = _fake(g, resident)
     monkeypatch.setattr(pkg, "NPlayerSolver", fake)
     monkeypatch.setattr(bench, "_timed", lambda s, steps: (ONE_S, ONE_S) if s.one_launch
