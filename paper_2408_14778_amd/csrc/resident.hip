@@ -794,11 +794,13 @@ void launch_resident(const Resident<F>& r, const UpdateRule& rule, bool alternat
     const int32_t most = resident_launch_iterations(r, passes);
     const size_t lds = lds_bytes(r);
     // workgroups go to the XCDs in turn: eight per member of a one-XCD team bring them to each
-    const int32_t grid = r.mode == RES_SOLO ? 1 : r.team_size <= kResXcd ? 8 * r.team_size : r.team_size;
+    Resident<F> team = r;
+    team.team_size = resident_workgroups(r);
+    const int32_t grid = team.team_size <= kResXcd && r.mode == RES_TEAM ? 8 * team.team_size : team.team_size;
     for (int32_t i = 0; i < n; i += most) {
         const int32_t m = std::min(most, n - i);
         auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(grid), dim3(r.threads), lds, st, r, rule, passes, m);
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(r.threads), lds, st, team, rule, passes, m);
         };
         if (r.players > 0) {
             const bool few = r.players <= 4;

@@ -34,6 +34,7 @@ struct Resident {
     int32_t ND = 0, Hp = 0, Qp = 0, Q0 = 0, D = 0;
     int32_t players = 0;   // general-sum game of n players, or 0 (two players, zero sum)
     int32_t mode = 0, bins = 0, team_size = 1, trunk_sets = 0;
+    int32_t team_limit = 0;  // at most so many workgroups (0: team_size of them)
     int32_t roots = 0, path_len = 0;
     int32_t max_nodes = 0, max_ranks = 0;
     int64_t n_con = 0;
@@ -67,6 +68,12 @@ void resident_shape(Resident<F>& r, const ResPlan& p);
 // Clears the team, once, when the solver is set up.
 template <class F>
 void launch_resident_reset(const Resident<F>& r, hipStream_t st);
+// Workgroups of a launch's team at most.
+template <class F>
+int32_t resident_workgroups(const Resident<F>& r) {
+    if (r.mode == RES_SOLO) return 1;
+    return r.team_limit > 0 && r.team_limit < r.team_size ? r.team_limit : r.team_size;
+}
 // The most iterations of one launch: about 5 ms of a full team's work. A launch keeps the team that it
 // formed; one that formed while other work held the CUs is slower, and the next launch forms anew. A
 // launch costs 6 to 10 us, so shorter ones would show. An iteration's time is taken as 4 us and 22 ps a

@@ -1273,6 +1273,14 @@ int cfr_build_partitioned(const cfr_game* game, const cfr_config* config, int32_
     return CFR_OK;
 }
 
+// Not part of the interface (tests): one-launch iterations by at most so many workgroups, as when other
+// work holds the CUs; 0: as planned.
+int cfr_internal_limit_team(cfr_solver* s, int32_t workgroups) {
+    if (s == nullptr || !s->resident || workgroups < 0) return set_err(CFR_EINVAL, "no team to limit");
+    s->res32.team_limit = s->res64.team_limit = workgroups;
+    return CFR_OK;
+}
+
 int cfr_iterate(cfr_solver* s, int32_t n) {
     if (s == nullptr || n < 0) return set_err(CFR_EINVAL, "bad solver or count");
     if (s->one_launch() && n > 0) {
@@ -1653,7 +1661,7 @@ int cfr_get_layout(cfr_solver* s, const char* name, void* out, int64_t bytes) {
     if (n == "one_launch") {
         const int32_t passes = !s->alternating ? 1 : s->players > 0 ? s->players : 2;
         const auto shape = [&](const auto& r) {
-            return std::array<int32_t, 4>{1, r.mode == cfr::RES_SOLO ? 1 : r.team_size, r.bins,
+            return std::array<int32_t, 4>{1, cfr::resident_workgroups(r), r.bins,
                                           cfr::resident_launch_iterations(r, passes)};
         };
         std::array<int32_t, 4> r{};
