@@ -743,6 +743,15 @@ __global__ void k_resident_reset(ResTeam* team) {
 }
 
 template <class F>
+__global__ void k_resident_pay(int64_t N, int64_t NB, int32_t cols, const int32_t* __restrict__ node,
+                               const F* __restrict__ payoff, F* __restrict__ pay) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (i >= NB) return;
+    const int32_t v = node[i];
+    for (int32_t c = 0; c < cols; ++c) pay[c * NB + i] = payoff[c * N + v];
+}
+
+template <class F>
 size_t lds_bytes(const Resident<F>& r) {
     const int64_t P = r.players > 0 ? r.players : 1, planes = r.players > 0 ? r.players : 2;
     const int64_t recs = ((r.max_ranks + 1) & ~1) * int64_t{r.mode == RES_SOLO ? 16 : 8};
@@ -783,6 +792,13 @@ void resident_shape(Resident<F>& r, const ResPlan& p) {
 }
 
 template <class F>
+void launch_resident_pay(const Resident<F>& r, const F* payoff, hipStream_t st) {
+    hipLaunchKernelGGL(k_resident_pay<F>, dim3(static_cast<unsigned>((r.NB + 255) / 256)), dim3(256), 0, st,
+                       r.N, r.NB, r.players > 0 ? r.players : 1, reinterpret_cast<const int32_t*>(r.val),
+                       payoff, r.pay);
+}
+
+template <class F>
 void launch_resident_reset(const Resident<F>& r, hipStream_t st) {
     hipLaunchKernelGGL(k_resident_reset, dim3(1), dim3(256), 0, st, r.team);
 }
@@ -815,6 +831,7 @@ void launch_resident(const Resident<F>& r, const UpdateRule& rule, bool alternat
 
 #define CFR_RES_INSTANTIATE(F)                                                                \
     template void resident_shape<F>(Resident<F>&, const ResPlan&);                            \
+    template void launch_resident_pay<F>(const Resident<F>&, const F*, hipStream_t);          \
     template void launch_resident_reset<F>(const Resident<F>&, hipStream_t);                  \
     template void launch_resident<F>(const Resident<F>&, const UpdateRule&, bool, int32_t,    \
                                      hipStream_t);

@@ -65,6 +65,10 @@ struct Resident {
 // Takes a plan's sizes and sets the launch shape.
 template <class F>
 void resident_shape(Resident<F>& r, const ResPlan& p);
+// Fills r.pay from the payoff columns in canonical order (column i at i N); r.val holds ResPlan::node
+// as int32 (it is not read before an iteration has written it).
+template <class F>
+void launch_resident_pay(const Resident<F>& r, const F* payoff, hipStream_t st);
 // Clears the team, once, when the solver is set up.
 template <class F>
 void launch_resident_reset(const Resident<F>& r, hipStream_t st);

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <atomic>
 #include <functional>
+#include <memory>
 #include <new>
 #include <thread>
 
@@ -155,8 +156,24 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
     const int64_t cols = columns(z), pl = planes(z), real = z.real_bytes;
     P = ResPlan{};
     if (!resident_fits(z)) return false;
-    for (int64_t v = 0; v < N; ++v)
-        if (L.node_player[v] == 0 && L.child_begin[v + 1] - L.child_begin[v] > kResMaxFan) return false;
+    // every node's level, and each level's largest fan-out of a chance node
+    const std::unique_ptr<int8_t[]> level(new int8_t[N]);
+    std::vector<int32_t> fan(D + 1, 1);
+    for (int32_t l = 0; l <= D; ++l) {
+        std::atomic<int32_t> most{1};
+        const int32_t lo = L.level_offset[l];
+        for_ranges(L.level_offset[l + 1] - lo, [&, l, lo](int64_t i0, int64_t i1) {
+            int32_t k = 1;
+            for (int64_t v = lo + i0; v < lo + i1; ++v) {
+                level[v] = static_cast<int8_t>(l);
+                if (L.node_player[v] == 0) k = std::max(k, L.child_begin[v + 1] - L.child_begin[v]);
+            }
+            for (int32_t seen = most; seen < k && !most.compare_exchange_weak(seen, k);) {
+            }
+        });
+        fan[l] = most;
+        if (fan[l] > kResMaxFan) return false;
+    }
     int64_t con = 0;
     for (int64_t h = 0; h < L.Hp; ++h)
         con += static_cast<int64_t>(L.member_offset[h + 1] - L.member_offset[h]) *
@@ -172,12 +189,9 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
         const int32_t h = L.node_infoset[p];
         return q_of[h] + (L.node_edge[v] - L.q_offset[h]);
     };
-    std::vector<int8_t> level(N, 0);
-    for (int32_t l = 0; l <= D; ++l)
-        for (int32_t v = L.level_offset[l]; v < L.level_offset[l + 1]; ++v)
-            level[v] = static_cast<int8_t>(l);
     // owner of every node: its bin (0: the trunk); bins' roots in order
-    std::vector<int32_t> roots, bin_root{0, 0}, in_trunk, sn, sd;
+    std::vector<int32_t> roots, bin_root{0, 0}, in_trunk;
+    std::unique_ptr<int32_t[]> sn, sd;
     std::vector<int8_t> trunk(N, 0);
     const int64_t solo = real * (cols * N + pl * nd + 3 * z.pairs + z.chance_pairs + con) + 16 * nd;
     if (N <= 65535 && solo <= kResLds) {
@@ -186,15 +200,22 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
         roots.push_back(0);
         bin_root = {0, 1};
     } else {
-        // nodes and decision nodes of every subtree
-        sn.assign(N, 1);
-        sd.assign(N, 0);
-        for (int64_t v = N - 1; v >= 0; --v) {
-            sd[v] += L.node_player[v] >= 0 ? 1 : 0;
-            if (v > 0) {
-                sn[L.parent[v]] += sn[v];
-                sd[L.parent[v]] += sd[v];
-            }
+        // nodes and decision nodes of every subtree, level by level from below
+        sn.reset(new int32_t[N]);
+        sd.reset(new int32_t[N]);
+        for (int32_t l = D; l >= 0; --l) {
+            const int32_t lo = L.level_offset[l];
+            for_ranges(L.level_offset[l + 1] - lo, [&, lo](int64_t i0, int64_t i1) {
+                for (int64_t v = lo + i0; v < lo + i1; ++v) {
+                    int32_t n = 1, d = L.node_player[v] >= 0 ? 1 : 0;
+                    for (int32_t c = L.child_begin[v]; c < L.child_begin[v + 1]; ++c) {
+                        n += sn[c];
+                        d += sd[c];
+                    }
+                    sn[v] = n;
+                    sd[v] = d;
+                }
+            });
         }
         int64_t first_want = std::min<int64_t>(kResTeam - 1, std::max<int64_t>(1, N / kBinNodes));
         // one XCD with the trunk
@@ -299,33 +320,28 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
         // wavefront
         const int32_t nodes = L.level_offset[l + 1] - L.level_offset[l];
         const bool grouped = z.players > 0 && nodes <= kWideNodes;
-        int32_t kmax = 1;
-        for (int32_t v = L.level_offset[l]; v < L.level_offset[l + 1]; ++v)
-            if (L.node_player[v] == 0)
-                kmax = std::max(kmax, L.child_begin[v + 1] - L.child_begin[v]);
         int32_t g = 0;
-        while (g < 6 && (1 << g) < kmax) ++g;
-        const bool wide = grouped && nodes <= kWideTop && kmax > 64;
+        while (g < 6 && (1 << g) < fan[l]) ++g;
+        const bool wide = grouped && nodes <= kWideTop && fan[l] > 64;
         glog[l] = g | (grouped ? kResGrouped : 0) | (wide ? kResWide : 0);
     }
-    std::vector<double> rc;
-    std::vector<int32_t> slot, lnode, lrank;
+    // per node, set where it is read: its first contribution, local node and local rank
+    std::unique_ptr<int32_t[]> slot, lnode, lrank;
     // chance products (rounded to float after every factor in single precision, as the level by
-    // level launches form them)
-    const auto chance_products = [&] {
-        const bool f64 = real == 8;
-        rc.assign(N, 1.0);
-        for (int64_t v = 1; v < N; ++v) {
-            if (L.node_player[v] < 0) continue;  // (terminal nodes need none)
-            const int32_t p = L.parent[v];
-            double x = rc[p];
-            if (L.node_player[p] == 0) {
-                const int64_t i = L.node_edge[v] - L.Qp;
-                x = f64 ? x * L.chance_prob64[i]
-                        : static_cast<double>(static_cast<float>(x) * L.chance_prob[i]);
-            }
-            rc[v] = x;
-        }
+    // level launches form them): x at v's parent to v
+    const auto chance_step = [&](double x, int64_t v) {
+        if (L.node_player[L.parent[v]] != 0) return x;
+        const int64_t i = L.node_edge[v] - L.Qp;
+        return real == 8 ? x * L.chance_prob64[i]
+                         : static_cast<double>(static_cast<float>(x) * L.chance_prob[i]);
+    };
+    const auto chance_product = [&](int64_t v) {
+        int64_t path[kResMaxDepth];
+        int32_t n = 0;
+        for (; v > 0; v = L.parent[v]) path[n++] = v;
+        double x = 1.0;
+        while (n > 0) x = chance_step(x, path[--n]);
+        return x;
     };
     // infosets: the trunk's first, then by pair (through the pairs: no sort); their contribution
     // slots in that order
@@ -341,20 +357,29 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
             for (int64_t q = 0; q < L.Qp; ++q)
                 if (at_pair[q] >= 0 && of_trunk[at_pair[q]] == pass) order.push_back(at_pair[q]);
         P.sets.resize(L.Hp);
-        slot.assign(N, 0);
+        std::vector<int32_t> base(L.Hp);
         int64_t at = 0;
         for (int64_t i = 0; i < L.Hp; ++i) {
             const int32_t h = order[i];
-            const int32_t m0 = L.member_offset[h], n = L.member_offset[h + 1] - m0;
+            const int32_t n = L.member_offset[h + 1] - L.member_offset[h];
             const int32_t k = L.q_offset[h + 1] - L.q_offset[h];
             P.trunk_sets += of_trunk[h];
             P.max_actions = std::max(P.max_actions, k);
             P.sets[i] = Rec4{q_of[h], static_cast<int32_t>(at), n, k | (L.infoset_player[h] << 24)};
-            for (int32_t j = 0; j < n; ++j)
-                slot[L.members[m0 + j]] =
-                    static_cast<int32_t>(at + static_cast<int64_t>(j) * res_stride(k, z.real_bytes));
+            base[h] = static_cast<int32_t>(at);
             at += static_cast<int64_t>(n) * res_stride(k, z.real_bytes);
         }
+        slot.reset(new int32_t[N]);
+        for_ranges(L.n_members, [&](int64_t m0, int64_t m1) {
+            int64_t h = std::upper_bound(L.member_offset.begin(), L.member_offset.end(), m0) -
+                        L.member_offset.begin() - 1;
+            for (int64_t m = m0; m < m1; ++m) {
+                while (m >= L.member_offset[h + 1]) ++h;
+                const int32_t k = L.q_offset[h + 1] - L.q_offset[h];
+                slot[L.members[m]] = base[h] + static_cast<int32_t>(m - L.member_offset[h]) *
+                                                   res_stride(k, z.real_bytes);
+            }
+        });
         P.mean_members = L.Hp > 0 ? static_cast<int32_t>(L.n_members / L.Hp) : 0;
         P.waves = gather_waves(L.n_members, L.Hp);
     };
@@ -366,9 +391,10 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
         P.rank_node.resize(nd);
         P.node.resize(N + P.roots);
     });
-    jobs.emplace_back([&] { lnode.assign(N, -1); });
-    jobs.emplace_back([&] { lrank.assign(N, -1); });
-    jobs.emplace_back(chance_products);
+    jobs.emplace_back([&] {
+        lnode.reset(new int32_t[N]);
+        lrank.reset(new int32_t[N]);
+    });
     jobs.emplace_back(number_sets);
     if (!run_all(N, jobs)) return false;
     // where each bin's ranks and nodes begin
@@ -420,6 +446,11 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
                     lrank[v] = r++;
                     ++t[l].w;
                 }
+            for (int32_t v : now) {
+                const bool apart = v == 0 || (team && !is_trunk && trunk[L.parent[v]]);
+                P.reach_c[rbase + lrank[v]] =
+                    apart ? chance_product(v) : chance_step(P.reach_c[rbase + lrank[L.parent[v]]], v);
+            }
             if (!now.empty()) {
                 l0 = l0 < 0 ? l : l0;
                 l1 = l;
@@ -449,8 +480,7 @@ bool plan_resident(const Layout& L, const std::vector<int32_t>& q_of, const ResS
             q.z = static_cast<int32_t>((root || v == 0 ? 0u : static_cast<uint32_t>(lrank[p])) |
                                        (actor << 16) | (static_cast<uint32_t>(k) << 20));
             q.w = v == 0 ? 0 : edge_of(v);
-            P.slot[rbase + d] = slot[v];
-            P.reach_c[rbase + d] = rc[v];
+            P.slot[rbase + d] = who > 0 ? slot[v] : 0;
             P.rank_node[rbase + d] = static_cast<int32_t>(v);
         }
         if (team && !is_trunk)

@@ -854,18 +854,21 @@ void member_slots(const cfr::Layout& L, std::vector<int32_t>& node_slot,
     slot_base[L.Hp] = static_cast<int32_t>(at);
 }
 
-// Copies a resident plan to the device and sets the launch shape.
+// Copies a resident plan to the device and sets the launch shape. Payoffs in the bins' order: `pay`, or
+// (null) gathered there from the canonical columns at `payoff` (device).
 template <class F>
 int upload_resident(cfr::Resident<F>& r, const cfr::ResPlan& p, const std::vector<F>& reach_c,
-                    const std::vector<F>& pay, hipStream_t st) {
+                    const std::vector<F>* pay, const F* payoff, hipStream_t st) {
     int rc;
     if ((rc = upload(r.rec, p.rec, st)) || (rc = upload(r.slot, p.slot, st)) ||
         (rc = upload(r.reach_c, reach_c, st)) || (rc = upload(r.sets, p.sets, st)) ||
         (rc = upload(r.root_rank, p.root_rank, st)) || (rc = upload(r.ext, p.ext, st)) ||
         (rc = upload(r.path, p.path, st)) || (rc = upload(r.table, p.table, st)) ||
-        (rc = upload(r.pay, pay, st)))
+        (rc = pay != nullptr ? upload(r.pay, *pay, st)
+                             : upload(reinterpret_cast<int32_t*>(r.val), p.node, st)))
         return rc;
     cfr::resident_shape(r, p);
+    if (pay == nullptr) cfr::launch_resident_pay(r, payoff, st);
     cfr::launch_resident_reset(r, st);
     return CFR_OK;
 }
@@ -914,17 +917,7 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
                                        std::to_string(need));
     // the resident records are planned beside the uploads of everything else
     cfr::ResPlan rp;
-    std::vector<float> reach_c32, res_pay32;
-    std::vector<double> res_pay64;
-    // payoffs in the bins' order
-    const auto in_bins = [&](const auto& pay, auto& out) {
-        const int64_t nb = static_cast<int64_t>(rp.node.size()), cols = players > 0 ? players : 1;
-        out.resize(cols * nb);
-        for (int64_t c = 0; c < cols; ++c)
-            cfr::for_ranges(nb, [&](int64_t i0, int64_t i1) {
-                for (int64_t i = i0; i < i1; ++i) out[c * nb + i] = pay[c * L.N + rp.node[i]];
-            });
-    };
+    std::vector<float> reach_c32;
     const auto plan_records = [&] {
         try {
             std::vector<int32_t> q_of(L.q_offset.begin(), L.q_offset.begin() + L.Hp);
@@ -932,8 +925,6 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
                 for (int64_t e = 0; e < L.Hp; ++e) q_of[P.infoset_canon[e]] = P.q_offset[e];
             if (!cfr::build_resident(L, q_of, resident_sizes(z), rp)) return false;
             if (!fp64) reach_c32.assign(rp.reach_c.begin(), rp.reach_c.end());
-            if (fp64) in_bins(players > 0 ? pay64 : L.payoff64, res_pay64);
-            else in_bins(players > 0 ? pay32 : L.payoff, res_pay32);
             return true;
         } catch (const std::bad_alloc&) {  // (the solver then runs level by level)
             return false;
@@ -1024,8 +1015,8 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     if (s->engine == ENGINE_BLOCK) cfr::launch_x_reset(s->xdev, st);
     if (s->resident) s->resident = plan_resident();
     if (s->resident) {
-        rc = fp64 ? upload_resident(s->res64, rp, rp.reach_c, res_pay64, st)
-                  : upload_resident(s->res32, rp, reach_c32, res_pay32, st);
+        rc = fp64 ? upload_resident<double>(s->res64, rp, rp.reach_c, nullptr, d64.payoff, st)
+                  : upload_resident<float>(s->res32, rp, reach_c32, nullptr, d.payoff, st);
         if (rc != CFR_OK) {
             discard(s);
             return rc;
@@ -2021,7 +2012,7 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
         s->resident = false;
     }
     if (s->resident) {
-        if ((rc = upload_resident(s->res32, rp, reach_c, pay, st)) != CFR_OK) {
+        if ((rc = upload_resident<float>(s->res32, rp, reach_c, &pay, nullptr, st)) != CFR_OK) {
             discard(s);
             return rc;
         }
