@@ -882,11 +882,6 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     const bool fp64 = (cfg.flags & CFR_FLAG_FP64) != 0;
     int rc = cfr::flatten(*game, L, err, fp64, players > 0 ? players : 2);
     if (rc != CFR_OK) return set_err(rc, err);
-    std::vector<float> pay32;
-    std::vector<double> pay64;
-    if (players > 0 && (rc = fp64 ? payoff_planes(L, players, payoff, pay64)
-                                  : payoff_planes(L, players, payoff, pay32)) != CFR_OK)
-        return rc;
     Sizes z;
     z.N = L.N; z.Hp = L.Hp; z.Qp = L.Qp; z.H0 = L.H0; z.Q0 = L.Q0; z.M = L.n_members;
     z.terminals = L.n_terminals;
@@ -912,10 +907,7 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
         z.resident = false;
         need = carve(d, d64, x, nullptr, z);
     }
-    if (bytes < need)
-        return set_err(CFR_ENOMEM, "workspace has " + std::to_string(bytes) + " bytes, needs " +
-                                       std::to_string(need));
-    // the resident records are planned beside the uploads of everything else
+    // the resident records are planned beside the payoffs and the uploads of everything else
     cfr::ResPlan rp;
     std::vector<float> reach_c32;
     const auto plan_records = [&] {
@@ -931,11 +923,19 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
         }
     };
     std::future<bool> records;  // (waits in its destructor)
-    if (z.resident) try {
+    if (z.resident && bytes >= need) try {
             records = std::async(std::launch::async, plan_records);
         } catch (...) {  // no thread: planned below
         }
     const auto plan_resident = [&] { return records.valid() ? records.get() : plan_records(); };
+    std::vector<float> pay32;
+    std::vector<double> pay64;
+    if (players > 0 && (rc = fp64 ? payoff_planes(L, players, payoff, pay64)
+                                  : payoff_planes(L, players, payoff, pay32)) != CFR_OK)
+        return rc;
+    if (bytes < need)
+        return set_err(CFR_ENOMEM, "workspace has " + std::to_string(bytes) + " bytes, needs " +
+                                       std::to_string(need));
     auto* s = new cfr_solver();
     carve(d, d64, x, workspace, z, &s->res32, &s->res64);
     s->dev = d;
