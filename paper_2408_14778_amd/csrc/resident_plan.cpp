@@ -45,15 +45,18 @@ int64_t planes(const ResSizes& z) { return z.players > 0 ? z.players : 2; }
 
 }  // namespace
 
+// Whether the public-block engine is the alternative.
+bool block_game(const ResSizes& z) { return z.players == 0 && z.real_bytes == 4 && z.level_pure; }
+
 int32_t resident_max_bins(const ResSizes& z) {
-    const bool block = z.players == 0 && z.real_bytes == 4 && z.level_pure;
-    return 1 + (z.forest ? kResRoundsForest : block ? kResRoundsBlock : kResRounds) * (kResTeam - 1);
+    return 1 + (z.forest ? kResRoundsForest : block_game(z) ? kResRoundsBlock : kResRounds) * (kResTeam - 1);
 }
 
 bool resident_fits(const ResSizes& z) {
     return z.decision > 0 && z.depth >= 1 && z.depth <= kResMaxDepth &&
            z.max_actions <= kResMaxActions && z.pairs + z.chance_pairs < (int64_t{1} << 28) &&
            z.players < 15 &&
+           (!block_game(z) || z.nodes <= (z.passes > 1 ? kResNodesBlock2 : kResNodesBlock)) &&
            z.real_bytes * (columns(z) * z.nodes + planes(z) * z.decision) <=
                kResLds * resident_max_bins(z) &&
            // (one round of bins that leaves them no room to be uneven is not worth its search)

@@ -23,14 +23,22 @@ constexpr int32_t kResMaxActions = 16;  // actions of its infosets
 constexpr int32_t kResMaxFan = 4095;    // children of a chance node
 constexpr int32_t kResTeam = 256;       // workgroups of a team: one per CU
 // Bins of a workgroup at most (it then loads each anew in every pass). Where the line lies: with the
-// public-block engine as the alternative (two players, single precision) three bins still win
-// (5.5 million nodes: 124 against 140 us per iteration; 3.3 million, two bins: 84 against 125 us),
-// the trend crosses near 7 million; the node engine's alternatives are two to four times slower
-// (2.2 million nodes in double precision, two bins: 78 against 229 us).
+// public-block engine as the alternative (two players, single precision) three bins still win, up to
+// kResNodesBlock nodes (5.5 million nodes: 124 against 140 us per iteration; 6.38 million of ten
+// ranks 136 against 135, 6.48 million of thirteen 135 against 147, 6.60 million of twelve 143 against
+// 135), and with two passes per iteration up to all that three bins hold, kResNodesBlock2 (6.60
+// million: 235 against 251 us, 6.89 million 236 against 282). The node engine's alternatives are two
+// times slower up to where eight bins end (2.2 million nodes in double precision: 78 against 229 us,
+// 8.3 million 286 against 518).
 // A batch keeps to one: its records cost more to lay out than its iterations gain beyond (10 games of
 // 2.8 million nodes in all, two bins: 103 -> 79 us per iteration for 66 ms; 12 of 1.6 million, one
 // bin: 84 -> 44 us).
+// A single game pays for its records when it is built: 2.2 million nodes in double precision 57 -> 67
+// ms, 3.3 million 87 -> 107 ms, 100,993 nodes 1.8 -> 2.6 ms, what 70, 120 and 13 iterations gain;
+// three players 64 ms and single precision, whose plan of public blocks takes several times as long,
+// the same within 2 %.
 constexpr int32_t kResRoundsBlock = 3, kResRounds = 8, kResRoundsForest = 1;
+constexpr int64_t kResNodesBlock = 6400000, kResNodesBlock2 = 7000000;
 constexpr int32_t kResMaxBins = 1 + kResRounds * (kResTeam - 1);
 constexpr int32_t kResTrunk = 32768;    // subtrees
 constexpr int32_t kResPath = 24;        // levels above them
@@ -52,6 +60,7 @@ constexpr int32_t res_stride(int32_t k, int32_t real_bytes) {
 struct ResSizes {
     int64_t nodes = 0, decision = 0, members = 0, infosets = 0, pairs = 0, chance_pairs = 0;
     int32_t depth = 0, max_actions = 0, players = 0, real_bytes = 4;
+    int32_t passes = 1;  // per iteration
     bool level_pure = true, forest = false;
 };
 // f(begin, end) over parts of 0 .. n - 1, on several threads where n is large. f does not throw.

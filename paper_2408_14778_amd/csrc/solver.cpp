@@ -139,6 +139,7 @@ struct Sizes {
     bool fp64 = false;       // values, probabilities and state in double precision
     int32_t players = 0;     // general-sum game of n rational players (node engine), else 0
     bool level_pure = true;
+    int32_t passes = 1;      // of an iteration (alternating updates: one per player)
     bool resident = false;   // small game: the resident iteration's records and state as well
     bool forest = false;     // a batch of n_games
     // node engine: regret contributions may be stored per child and gathered per infoset (false:
@@ -166,6 +167,10 @@ int choose_engine(bool level_pure, int32_t max_actions, uint32_t flags) {
     return ENGINE_BLOCK;
 }
 
+int32_t passes_of(uint32_t flags, int32_t players) {
+    return !(flags & CFR_FLAG_ALTERNATING) ? 1 : players > 0 ? players : 2;
+}
+
 cfr::ResSizes resident_sizes(const Sizes& z) {
     cfr::ResSizes r;
     const int32_t above = z.forest ? 1 : 0;  // a forest's games hang from a node of their own
@@ -173,7 +178,7 @@ cfr::ResSizes resident_sizes(const Sizes& z) {
     r.infosets = z.Hp; r.pairs = z.Qp; r.chance_pairs = z.Q0 + above * z.n_games;
     r.depth = z.D + above; r.max_actions = z.max_actions;
     r.players = z.players; r.real_bytes = z.fp64 ? 8 : 4; r.level_pure = z.level_pure;
-    r.forest = z.forest;
+    r.forest = z.forest; r.passes = z.passes;
     return r;
 }
 
@@ -552,6 +557,7 @@ int plan_impl(const cfr_game* game, const cfr_config* config, int32_t players,
     z.fp64 = config != nullptr && (config->flags & CFR_FLAG_FP64) != 0;
     z.players = players;
     z.level_pure = L.level_pure;
+    z.passes = passes_of(config ? config->flags : 0u, players);
     z.resident = choose_resident(z, config ? config->flags : 0u);
     cfr::Dev d{};
     cfr::Dev64 d64{};
@@ -891,6 +897,7 @@ int build_impl(const cfr_game* game, const cfr_config& cfg, int32_t players, con
     z.fp64 = fp64;
     z.players = players;
     z.level_pure = L.level_pure;
+    z.passes = passes_of(cfg.flags, z.players);
     z.resident = choose_resident(z, cfg.flags);
     cfr::ExecPlan P;
     if (z.engine == ENGINE_BLOCK) {
@@ -1896,6 +1903,7 @@ int cfr_plan_batch(const cfr_game* games, int32_t n_games, const cfr_config* con
     }
     z.packs = z.max_actions <= 4 && config != nullptr && (config->flags & CFR_FLAG_SUBTREE_PACKS);
     z.forest = true;
+    z.passes = passes_of(config != nullptr ? config->flags : 0u, 0);
     z.resident = choose_resident(z, config != nullptr ? config->flags : 0);
     cfr::Dev d{};
     cfr::Dev64 d64{};
@@ -1952,6 +1960,7 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     z.n_games = n_games;
     z.packs = max_actions <= 4 && (cfg.flags & CFR_FLAG_SUBTREE_PACKS);
     z.forest = true;
+    z.passes = passes_of(cfg.flags, z.players);
     z.resident = choose_resident(z, cfg.flags);
     cfr::Dev d{};
     cfr::Dev64 d64{};
