@@ -79,6 +79,22 @@ void forward(cfr_mlp* n, const void* x, int32_t B) {
                      nullptr, A, n->st);
 }
 
+// Pinned memory for a step's loss. A network makes it ready when it is created; without a device, which
+// creating one does not need, it is left to the first step that asks for a loss.
+bool pin_loss(cfr_mlp* n) {
+    if (n->h_loss != nullptr) return true;
+    // (allocating touches no stream: a capture that this thread is in the middle of goes on)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    const hipError_t e =
+        hipHostMalloc(reinterpret_cast<void**>(&n->h_loss), sizeof(float), hipHostMallocDefault);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (e == hipSuccess) return true;
+    n->h_loss = nullptr;
+    (void)hipGetLastError();
+    return false;
+}
+
 // Refreshes the transposed weight copies from wb.
 void transpose_weights(cfr_mlp* n) {
     int64_t o[7], t[3];
@@ -125,11 +141,7 @@ int cfr_mlp_create(int32_t in_features, int32_t hidden, int32_t outputs, int32_t
     }
     n->st = static_cast<hipStream_t>(stream);
     n->step = 0;
-    if (hipHostMalloc(reinterpret_cast<void**>(&n->h_loss), sizeof(float), hipHostMallocDefault) !=
-        hipSuccess) {
-        delete n;
-        return cfr::set_error(CFR_ENOMEM, "pinned host memory for the loss");
-    }
+    (void)pin_loss(n);
     *out = n;
     return CFR_OK;
 }
@@ -189,6 +201,8 @@ int cfr_mlp_train_step(cfr_mlp* n, const void* x, const float* target, const flo
                        int32_t B, float lr, float* loss) {
     if (n == nullptr || x == nullptr || target == nullptr || mask == nullptr || B < 1 || B > n->maxB)
         return cfr::set_error(CFR_EINVAL, "bad batch or null argument");
+    if (loss != nullptr && !pin_loss(n))
+        return cfr::set_error(CFR_ENOMEM, "pinned host memory for the loss");
     int64_t o[7];
     offsets(n->F, n->H, n->A, o);
     const int F = n->F, H = n->H, A = n->A;
@@ -245,7 +259,7 @@ int cfr_mlp_train_step(cfr_mlp* n, const void* x, const float* target, const flo
 int cfr_mlp_destroy(cfr_mlp* n) {
     if (n == nullptr) return CFR_OK;
     (void)hipStreamSynchronize(n->st);
-    (void)hipHostFree(n->h_loss);
+    if (n->h_loss != nullptr) (void)hipHostFree(n->h_loss);
     delete n;
     return CFR_OK;
 }
