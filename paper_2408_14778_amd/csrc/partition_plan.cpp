@@ -19,7 +19,8 @@ int64_t down(const Layout& L, int64_t x, int32_t from, int32_t to) {
 
 }  // namespace
 
-int plan_partitions(const Layout& L, int32_t cut, int64_t max_window, PartPlan& P, std::string& err) {
+int plan_partitions(const Layout& L, int32_t cut, int64_t max_window, PartPlan& P, std::string& err,
+                    bool links) {
     const int32_t D = L.D;
     if (D < 2 || cut < 1 || cut > D - 1) {
         err = "cut level must lie in 1 .. depth - 1 (depth " + std::to_string(D) + ")";
@@ -63,9 +64,11 @@ int plan_partitions(const Layout& L, int32_t cut, int64_t max_window, PartPlan& 
     P.off.assign(P.parts + 1, 0);
     P.lo.assign(static_cast<size_t>(P.parts) * (nl + 1), 0);
     P.patch_off.assign(P.parts + 1, 0);
-    P.parent.resize(P.total);
+    if (links) {
+        P.parent.resize(P.total);
+        P.edge.resize(P.total);
+    }
     P.infoset.resize(P.total);
-    P.edge.resize(P.total);
     P.player.resize(P.total);
     P.value0.resize(P.total);
     P.child_begin.resize(P.total + P.parts);
@@ -91,16 +94,18 @@ int plan_partitions(const Layout& L, int32_t cut, int64_t max_window, PartPlan& 
         for (int32_t l = cut + 1; l <= D; ++l) {
             for (int64_t g = g_lo[l]; g < g_hi[l]; ++g) {
                 const int64_t i = off[l] + (g - g_lo[l]);
-                const int32_t par = L.parent[g];
-                P.parent[o + i] = l == cut + 1
-                                      ? par
-                                      : static_cast<int32_t>(P.base + off[l - 1] + (par - g_lo[l - 1]));
+                if (links) {
+                    const int32_t par = L.parent[g];
+                    P.parent[o + i] = l == cut + 1 ? par
+                                                   : static_cast<int32_t>(P.base + off[l - 1] +
+                                                                          (par - g_lo[l - 1]));
+                    P.edge[o + i] = L.node_edge[g];
+                }
                 cb[i] = l < D ? static_cast<int32_t>(P.base + off[l + 1] +
                                                      (L.child_begin[g] - g_lo[l + 1]))
                               : static_cast<int32_t>(P.base + w);
                 P.player[o + i] = L.node_player[g];
                 P.infoset[o + i] = L.node_infoset[g];
-                P.edge[o + i] = L.node_edge[g];
                 P.value0[o + i] = L.node_player[g] < 0 ? (f64 ? L.payoff64[g] : L.payoff[g]) : 0.0;
             }
         }

@@ -25,7 +25,7 @@ struct PartPlan {
     std::vector<int32_t> lo;       // per partition, local level offsets of levels cut + 1 .. D + 1
     std::vector<int64_t> patch_off;  // per partition, its level-cut child_begin patch (b - a + 1)
     // host arrays, partition-major (node arrays: off[p] + i; child_begin: off[p] + p + i)
-    std::vector<int32_t> parent, child_begin, infoset, edge;
+    std::vector<int32_t> parent, child_begin, infoset, edge;  // (parent, edge: links below)
     std::vector<int8_t> player;
     std::vector<double> value0;    // the payoff at terminal nodes, 0 elsewhere
     std::vector<int32_t> patch;    // level-cut child_begin entries, local, per partition
@@ -34,7 +34,8 @@ struct PartPlan {
 // Plans the partitions of layout L cut at level `cut` (1 <= cut <= D - 1), grouping consecutive
 // level-cut subtrees while their window nodes stay within max_window (a larger subtree is a
 // partition of its own; terminal level-cut nodes join the current partition). CFR_OK or
-// CFR_EINVAL with a message.
-int plan_partitions(const Layout& L, int32_t cut, int64_t max_window, PartPlan& P, std::string& err);
+// CFR_EINVAL with a message. links: parent and edge too (checks of the plan; the solver reads neither).
+int plan_partitions(const Layout& L, int32_t cut, int64_t max_window, PartPlan& P, std::string& err,
+                    bool links = true);
 
 }  // namespace cfr

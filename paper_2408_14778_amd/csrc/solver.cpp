@@ -1131,7 +1131,7 @@ int cfr_plan_partitioned(const cfr_game* game, const cfr_config* config, int32_t
     int rc = cfr::flatten(*game, L, err, fp64);
     if (rc != CFR_OK) return set_err(rc, err);
     cfr::PartPlan P;
-    if ((rc = cfr::plan_partitions(L, cut_level, max_window_nodes, P, err)) != CFR_OK)
+    if ((rc = cfr::plan_partitions(L, cut_level, max_window_nodes, P, err, false)) != CFR_OK)
         return set_err(rc, err);
     cfr::StreamPlan stream_plan;
     cfr::plan_stream(L, P, fp64, stream_plan, true);
@@ -1172,7 +1172,7 @@ int cfr_build_partitioned(const cfr_game* game, const cfr_config* config, int32_
     int rc = cfr::flatten(*game, L, err, fp64);
     if (rc != CFR_OK) return set_err(rc, err);
     cfr::PartPlan P;
-    if ((rc = cfr::plan_partitions(L, cut_level, max_window_nodes, P, err)) != CFR_OK)
+    if ((rc = cfr::plan_partitions(L, cut_level, max_window_nodes, P, err, false)) != CFR_OK)
         return set_err(rc, err);
     cfr::StreamPlan stream_plan;
     cfr::plan_stream(L, P, fp64, stream_plan);
