@@ -147,24 +147,32 @@ int cfr_build(const cfr_game* game, const cfr_config* config, void* workspace, s
               void* stream, cfr_solver** out);
 
 /* Enqueue n iterations (Section 3.2) on the solver's stream; does not synchronise. A game whose
- * subtrees fit the LDS of the chip's CUs a few times over (in single precision up to about 6 million
- * nodes; a batch up to about 2 million) runs all n in one launch, unless the configuration asks for the
- * level-by-level kernels (CFR_FLAG_NO_GRAPH, CFR_FLAG_SUBTREE_PACKS, CFR_FLAG_KEEP_NODE_VALUES, or for
- * two players CFR_FLAG_NODE_ENGINE) or the workspace has room for those alone; any other game replays
- * its captured iteration n times. Two-player single-precision results are the same bit for bit. */
+ * subtrees fit the LDS of the chip's CUs a few times over (two players in single precision up to 6.4
+ * million nodes, 7 million with alternating updates; other games up to about 8 million; a batch up to
+ * about 2 million) runs whole iterations in one launch (about 5 ms of them each), unless the
+ * configuration asks for the level-by-level kernels (CFR_FLAG_NO_GRAPH, CFR_FLAG_SUBTREE_PACKS,
+ * CFR_FLAG_KEEP_NODE_VALUES, or for two players CFR_FLAG_NODE_ENGINE), launch shapes were asked for
+ * (cfr_set_launch_shape) or the workspace has room for those alone; any other game replays its captured
+ * iteration n times. Results do not depend on the way, bit for bit, for general-sum games and for two
+ * players in single precision on the public-block engine (there but for an infoset larger than a
+ * chunk of the level-by-level launches, whose order of sums is their shape's); the node engine's
+ * two-player sums, which its launches add by atomics in any order, agree to rounding. A launch works
+ * with the CUs that are free when it begins: where solvers' calls overlap, the later one runs on fewer
+ * until its next launch. */
 int cfr_iterate(cfr_solver* s, int32_t n);
 
 /* Run n iterations with direct launches and a pair of hipEvents around every kernel launch on
  * the solver's stream (synchronises). kernel_ms[k] receives the summed event time of kernel
  * kind k over the n iterations and kernel_launches[k] its launch count, for k < n_kinds;
- * cfr_kernel_name(k) names kind k (empty string past the last kind). The results of the
- * iterations are the same as cfr_iterate's. */
+ * cfr_kernel_name(k) names kind k (empty string past the last kind). These are always the
+ * level-by-level kernels, also where cfr_iterate runs whole iterations in one launch; the results of
+ * the iterations are cfr_iterate's, as exactly as that says. */
 int cfr_iterate_timed(cfr_solver* s, int32_t n, double* kernel_ms, int64_t* kernel_launches,
                       int32_t n_kinds);
 const char* cfr_kernel_name(int32_t kind);
 
-/* Like cfr_iterate_timed but per launch: after n iterations, for each of the *n_launches
- * launches of one iteration (in launch order, up to max_launches are written), the summed
+/* Like cfr_iterate_timed (the level-by-level kernels) but per launch: after n iterations, for each
+ * of the *n_launches launches of one iteration (in launch order, up to max_launches are written), the summed
  * event time over the n iterations, its kernel kind (cfr_kernel_name), the tree level it
  * processes (-1: the single-workgroup launch of the first levels; -2: the launch that takes
  * several small top-down levels at once) and its number of work items. Synchronises. */
@@ -258,14 +266,15 @@ int cfr_get_node_values_f64(cfr_solver* s, double* u1, double* reach, int64_t n_
  * chance as for cfr_plan, with infoset_player in 0 (chance) .. n_players; its payoff_u1 and
  * payoff_u2 are ignored. payoff (host, n_nodes * n_players doubles, node-major in input node
  * order): u(t, i) at payoff[t * n_players + (i - 1)], read at terminals only and required
- * finite there. 2 <= n_players <= 8. The solver runs the node engine (FP32, or FP64 with
- * CFR_FLAG_FP64) with every player's infosets updated in one pass (CFR_FLAG_ALTERNATING: a
+ * finite there. 2 <= n_players <= 8. The solver runs the node engine's arithmetic (FP32, or FP64 with
+ * CFR_FLAG_FP64; its launches or, as cfr_iterate says, one for whole iterations) with every player's
+ * infosets updated in one pass (CFR_FLAG_ALTERNATING: a
  * pass per player in seat order, each under the strategies the earlier passes produced, the
  * iteration counted by the last): at a node d of player i in
  * infoset h the regret r~(h, a) gathers pi_{-i}(d) (w_a[i] - u[i]), pi_{-i} the product of
  * chance's and the other players' reaches, and u the node's payoff vector. No step adds by
  * atomics, so the results do not depend on scheduling: the same game, configuration and state
- * give the same bits on every run. cfr_iterate,
+ * give the same bits on every run, whichever launches it takes. cfr_iterate,
  * cfr_get_state / cfr_set_state, cfr_average_strategy, cfr_current_strategy (and their _f64
  * forms), cfr_get_layout and cfr_destroy apply unchanged. cfr_exploitability returns
  * CFR_EINVAL (Section 2.2 defines it for two-player zero-sum games), as do cfr_get_node_values

@@ -51,7 +51,8 @@ bool launch_mlp_forward(int M, int F, int H, int A, const void* X, const void* W
 // Whether the fused forward pass takes a shape: F a multiple of 16 up to 128, H 64, 128 or 256, A
 // at most 8, X 16-byte aligned.
 bool mlp_fused_shape(int F, int H, int A, const void* X);
-// A training step in three launches for those shapes and at least 64 rows: the rows' forward and
+// A training step in three launches for those shapes, of any number of rows that kMaxLossParts
+// workgroups take: the rows' forward and
 // backward pass, the gradients' partials, and the update of the weights and all their copies. The
 // weights, moments and gradients equal those of the per-layer launches bit for bit. False:
 // nothing launched.

@@ -1,4 +1,4 @@
-// Resident iteration (device): one launch runs any number of iterations of a game whose bins
+// Resident iteration (device): one launch runs many iterations of a game whose bins
 // (resident_plan.hpp) fit the LDS of the chip's CUs.
 #pragma once
 

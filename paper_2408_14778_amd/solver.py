@@ -223,7 +223,8 @@ class Solver:
         N.check(self._lib.cfr_iterate(self._h, int(n)))
 
     def iterate_timed(self, n: int) -> dict:
-        """n iterations with hipEvents around every kernel launch: {kernel: (launches, ms)}."""
+        """n iterations of the level-by-level kernels (also where iterate() takes one launch) with
+        hipEvents around every kernel launch: {kernel: (launches, ms)}."""
         kinds = 16
         ms = np.zeros(kinds, dtype=np.float64)
         cnt = np.zeros(kinds, dtype=np.int64)
@@ -237,7 +238,8 @@ class Solver:
         return out
 
     def iterate_profile(self, n: int) -> list:
-        """n iterations; per launch of one iteration: kernel, level, work items, mean ms."""
+        """n iterations of the level-by-level kernels; per launch of one iteration: kernel, level,
+        work items, mean ms."""
         cap = 4096
         ms = np.zeros(cap, dtype=np.float64)
         kind = np.zeros(cap, dtype=np.int32)
@@ -359,7 +361,7 @@ class Solver:
 
 class NPlayerSolver(Solver):
     """CFR over a general-sum game of n rational players (``game.payoff``: one payoff column
-    per player, Section 3.1) on the node engine, through cfr_plan_n / cfr_build_n: vanilla,
+    per player, Section 3.1) in the node engine's arithmetic, through cfr_plan_n / cfr_build_n: vanilla,
     CFR+ or discounted, every player's infosets updated in one pass (``schedule``
     'simultaneous') or a pass per player in seat order ('alternating'), precision 'f32' or 'f64'.
     State, strategies and iteration work as in Solver; exploitability() raises (it is defined
