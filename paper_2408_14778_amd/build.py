@@ -9,7 +9,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libcfr_mi355x.so")
 SOURCES = ["flatten.cpp", "xplan.cpp", "host_layout.cpp", "partition_plan.cpp",
-           "stream_plan.cpp", "partition.hip",
+           "stream_plan.cpp", "partition.hip", "pinned.cpp",
            "resident_plan.cpp", "resident.hip",
            "solver.cpp", "mlp_api.cpp", "kernels.hip", "xkernels.hip", "mlp.hip", "mlp_noalloc.hip"]
 

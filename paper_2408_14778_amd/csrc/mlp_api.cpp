@@ -9,6 +9,7 @@
 #include "../../include/cfr_warmstart.h"
 #include "mlp.hpp"
 #include "mlp_net.hpp"
+#include "pinned.hpp"
 
 namespace cfr {
 int set_error(int code, const std::string& msg);  // solver.cpp
@@ -79,20 +80,11 @@ void forward(cfr_mlp* n, const void* x, int32_t B) {
                      nullptr, A, n->st);
 }
 
-// Pinned memory for a step's loss. A network makes it ready when it is created; without a device, which
+// A pinned word for a step's loss. A network makes it ready when it is created; without a device, which
 // creating one does not need, it is left to the first step that asks for a loss.
 bool pin_loss(cfr_mlp* n) {
-    if (n->h_loss != nullptr) return true;
-    // (allocating touches no stream: a capture that this thread is in the middle of goes on)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    const hipError_t e =
-        hipHostMalloc(reinterpret_cast<void**>(&n->h_loss), sizeof(float), hipHostMallocDefault);
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (e == hipSuccess) return true;
-    n->h_loss = nullptr;
-    (void)hipGetLastError();
-    return false;
+    if (n->h_loss == nullptr) n->h_loss = static_cast<float*>(cfr::pinned_take(sizeof(float)));
+    return n->h_loss != nullptr;
 }
 
 // Refreshes the transposed weight copies from wb.
@@ -259,7 +251,7 @@ int cfr_mlp_train_step(cfr_mlp* n, const void* x, const float* target, const flo
 int cfr_mlp_destroy(cfr_mlp* n) {
     if (n == nullptr) return CFR_OK;
     (void)hipStreamSynchronize(n->st);
-    if (n->h_loss != nullptr) (void)hipHostFree(n->h_loss);
+    cfr::pinned_give(n->h_loss);
     delete n;
     return CFR_OK;
 }

@@ -818,8 +818,8 @@ void launch_resident(const Resident<F>& r, const UpdateRule& rule, bool alternat
     Resident<F> team = r;
     team.team_size = resident_workgroups(r);
     const int32_t grid = team.team_size <= kResXcd && r.mode == RES_TEAM ? 8 * team.team_size : team.team_size;
-    for (int32_t i = 0; i < n; i += most) {
-        const int32_t m = std::min(most, n - i);
+    for (int64_t i = 0; i < n; i += most) {
+        const int32_t m = static_cast<int32_t>(std::min<int64_t>(most, n - i));
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(r.threads), lds, st, team, rule, passes, m);
         };

@@ -23,6 +23,7 @@
 #include "mlp.hpp"
 #include "kernels.hpp"
 #include "partition.hpp"
+#include "pinned.hpp"
 #include "resident.hpp"
 #include "xkernels.hpp"
 #include "xplan.hpp"
@@ -42,7 +43,7 @@ struct cfr_solver {
     ~cfr_solver() {
         if (part32) part32->release();
         if (part64) part64->release();
-        if (br_out != nullptr) (void)hipHostFree(br_out);
+        cfr::pinned_give(br_out);
     }
     double* br_out = nullptr;  // pinned: the best-response values, written by the kernels in place
     // small game: whole iterations in one launch (the one of the solver's precision is set up)
@@ -438,10 +439,8 @@ void discard(cfr_solver* s) {
 // Pinned memory for a solver's best-response values (a copy to the caller's own memory would go through
 // a staging launch and a second wait: 11 us of a check).
 int best_response_out(cfr_solver* s) {
-    if (hipHostMalloc(reinterpret_cast<void**>(&s->br_out), 2 * sizeof(double) * s->n_games,
-                      hipHostMallocDefault) == hipSuccess)
-        return CFR_OK;
-    s->br_out = nullptr;
+    s->br_out = static_cast<double*>(cfr::pinned_take(2 * sizeof(double) * s->n_games));
+    if (s->br_out != nullptr) return CFR_OK;
     return set_err(CFR_ENOMEM, "pinned host memory for the best-response values");
 }
 
