@@ -26,3 +26,9 @@ def test_line_of_single_precision_games():
     assert large.n_nodes == 6596371
     assert not _one_launch(large)
     assert _one_launch(large, schedule="alternating") and _one_launch(large, precision="f64")
+
+
+def test_no_workspace_for_records_that_cannot_fit(large_game):
+    """21.5 million nodes in double precision: three times what eight bins per workgroup hold."""
+    assert not _one_launch(large_game, precision="f64")
+    assert not _one_launch(large_game) and not _one_launch(large_game, schedule="alternating")
