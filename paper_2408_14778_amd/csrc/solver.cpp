@@ -1991,6 +1991,36 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     std::vector<float> prob_tail(F.Qp + F.Q0, 0.0f);
     std::copy(F.chance_prob.begin(), F.chance_prob.end(), prob_tail.begin() + F.Qp);
     if (z.resident) prob_tail.resize(F.Qp + F.Q0 + n_games, 1.0f);
+    // the resident records are planned beside the uploads of everything else
+    cfr::ResPlan rp;
+    std::vector<float> reach_c, pay;
+    const auto plan_records = [&] {
+        try {
+            const cfr::Layout L = cfr::forest_layout(layouts);
+            // each infoset's pairs in the plan: by the input pair of its first
+            std::vector<int32_t> pair_of(F.Qp), q_of(F.Hp);
+            for (int64_t q = 0; q < F.Qp; ++q) pair_of[F.q_input[q]] = static_cast<int32_t>(q);
+            int64_t h = 0, in = 0;
+            for (const cfr::Layout& G : layouts) {
+                for (int64_t i = 0; i < G.Hp; ++i) q_of[h++] = pair_of[in + G.q_input[G.q_offset[i]]];
+                in += G.Qp;
+            }
+            if (!cfr::build_resident(L, q_of, resident_sizes(z), rp)) return false;
+            pay.resize(rp.node.size());
+            cfr::for_ranges(static_cast<int64_t>(pay.size()), [&](int64_t i0, int64_t i1) {
+                for (int64_t i = i0; i < i1; ++i) pay[i] = L.payoff[rp.node[i]];
+            });
+            reach_c.assign(rp.reach_c.begin(), rp.reach_c.end());
+            return true;
+        } catch (const std::bad_alloc&) {  // (the batch then runs level by level)
+            return false;
+        }
+    };
+    std::future<bool> records;  // (waits in its destructor)
+    if (z.resident) try {
+            records = std::async(std::launch::async, plan_records);
+        } catch (...) {  // no thread: planned below
+        }
     cfr_default_launch_shape(&s->shape);
     if ((rc = upload_plan(s, F, st)) || (rc = upload(d.prob, prob_tail, st))) {
         discard(s);
@@ -1998,27 +2028,7 @@ int cfr_build_batch(const cfr_game* games, int32_t n_games, const cfr_config* co
     }
     cfr::launch_reset(d, st, false);
     cfr::launch_x_reset(s->xdev, st);
-    cfr::ResPlan rp;
-    std::vector<float> reach_c, pay;
-    if (z.resident) try {
-        const cfr::Layout L = cfr::forest_layout(layouts);
-        // each infoset's pairs in the plan: by the input pair of its first
-        std::vector<int32_t> pair_of(F.Qp), q_of(F.Hp);
-        for (int64_t q = 0; q < F.Qp; ++q) pair_of[F.q_input[q]] = static_cast<int32_t>(q);
-        int64_t h = 0, in = 0;
-        for (const cfr::Layout& G : layouts) {
-            for (int64_t i = 0; i < G.Hp; ++i) q_of[h++] = pair_of[in + G.q_input[G.q_offset[i]]];
-            in += G.Qp;
-        }
-        s->resident = cfr::build_resident(L, q_of, resident_sizes(z), rp);
-        pay.resize(rp.node.size());
-        cfr::for_ranges(static_cast<int64_t>(pay.size()), [&](int64_t i0, int64_t i1) {
-            for (int64_t i = i0; i < i1; ++i) pay[i] = L.payoff[rp.node[i]];
-        });
-        reach_c.assign(rp.reach_c.begin(), rp.reach_c.end());
-    } catch (const std::bad_alloc&) {  // (the batch then runs level by level)
-        s->resident = false;
-    }
+    if (z.resident) s->resident = records.valid() ? records.get() : plan_records();
     if (s->resident) {
         if ((rc = upload_resident<float>(s->res32, rp, reach_c, &pay, nullptr, st)) != CFR_OK) {
             discard(s);
